@@ -95,6 +95,32 @@ __host__ __device__ __forceinline__ int64_t box_row_start(int64_t X, int64_t Y, 
   return box_prefix(Z, LZ) * SY * SX + cz * box_prefix(Y, LY) * SX + cyz * box_prefix(X, LX);
 }
 
+// Segment length of a marching kernel: `layers` steps per tile, split into
+// segments of equal length, each of which takes `extra` steps more when there
+// are several (the layer below it, integrated again for its carry, and its
+// start).  The waves run in rounds over the chip's `slots` resident waves, so
+// a launch takes about ceil(waves / slots) x (length + extra) steps; the length
+// with the fewest is taken, so that neither the last round nor, on a small
+// mesh, the chip is left mostly idle.  `tiles`: waves per segment (all batch
+// entries).  Short segments are what a small mesh needs: H1 p = 2 on 4^3
+// elements (4 tiles) takes 48 us as segments of 8 layers and 11 us of 1 layer,
+// p = 5 on 13 x 9 x 11 47.7 us of 8 and 30.1 us of 4.
+inline int64_t march_segment(int64_t layers, int64_t tiles, int64_t slots, int64_t extra) {
+  constexpr int64_t kMaxSegments = 65535;  // second grid dimension
+  int64_t seglen = layers, best = -1;
+  for (int64_t len = 1; len <= layers; ++len) {
+    const int64_t ns = ceil_div(layers, len);
+    if (ns > kMaxSegments) continue;
+    if (ns > 1 && ceil_div(layers, ns) != len) continue;  // same split as a shorter length
+    const int64_t cost = ceil_div(tiles * ns, slots) * (len + (ns > 1 ? extra : 0));
+    if (best < 0 || cost < best) {
+      best = cost;
+      seglen = len;
+    }
+  }
+  return seglen;
+}
+
 template <typename T>
 inline T* dev_at(const lor_sched* s, size_t off) {
   return reinterpret_cast<T*>(static_cast<char*>(s->dev) + off);

@@ -39,8 +39,6 @@
 // same code).  The matrix is therefore bitwise symmetric and deterministic.
 // All sums are FP64, in the FP32 form too (each finished entry is rounded
 // once).
-#include <algorithm>
-
 #include "lor_common.hpp"
 #include "lor_h1_math.hpp"
 
@@ -540,23 +538,9 @@ static int launch_owner(const lor_sched* sched, int batch, const void* kappa, do
   const int64_t ntx = ceil_div(NXc, kOwnStride), nty = ceil_div(NYc, kOwnStride);
   const int64_t tiles = ntx * nty;
   if (tiles > INT32_MAX) LOR_FAIL(LOR_EOVERFLOW, "too many owner-computes tiles");
-  // Split the z-march into segments (a segment above the bottom costs one
-  // extra cell layer).  The waves run in rounds over the chip's wave slots
-  // (CUs x resident waves per CU), so the launch takes about
-  // ceil(waves / slots) x (layers per wave + 1) layer steps: pick the segment
-  // length (at least 8 layers) that minimises it, so that the last round is
-  // not left mostly idle.
+  // segments along z: one above the bottom integrates the layer below it too
   const int64_t slots = static_cast<int64_t>(owner_num_cus()) * OwnCfg<T, R>::WPC;
-  int64_t seglen = NZc, best = -1;
-  for (int64_t len = std::min<int64_t>(8, NZc); len <= NZc; ++len) {
-    const int64_t ns = ceil_div(NZc, len);
-    if (ns > 1 && ceil_div(NZc, ns) != len) continue;  // same split as a shorter length
-    const int64_t cost = ceil_div(tiles * ns * batch, slots) * (len + 1);
-    if (best < 0 || cost < best) {
-      best = cost;
-      seglen = len;
-    }
-  }
+  const int64_t seglen = march_segment(NZc, tiles * batch, slots, 1);
   const int64_t nseg = ceil_div(NZc, seglen);
   dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>(nseg), static_cast<unsigned>(batch));
   (void)row_ptr;  // the rows start where the lattice puts them (the pattern call checked row_ptr)

@@ -496,16 +496,7 @@ static int launch_nd_owner_dir(const lor_sched* s, int batch, const int32_t* ele
   }
   const int64_t slots = static_cast<int64_t>(num_cus_nd()) * ((dev >= 0 && dev < 64) ? wpc[dev] : 1);
   const int64_t tiles = static_cast<int64_t>(nt1) * nt2;
-  int64_t seglen = L[M], best = -1;
-  for (int64_t len = 1; len <= L[M]; ++len) {
-    const int64_t ns = ceil_div(L[M], len);
-    if (ns > 1 && ceil_div(L[M], ns) != len) continue;  // same split as a shorter length
-    const int64_t cost = ceil_div(tiles * ns * batch, slots) * len;
-    if (best < 0 || cost < best) {
-      best = cost;
-      seglen = len;
-    }
-  }
+  const int64_t seglen = march_segment(L[M], tiles * batch, slots, 0);
   const int nseg = static_cast<int>(ceil_div(L[M], seglen));
   dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>(nseg), static_cast<unsigned>(batch));
   k_nd_owner<P, T, R, M><<<grid, 64, 0, st>>>(nex, ney, nez, nt1, static_cast<int>(seglen),

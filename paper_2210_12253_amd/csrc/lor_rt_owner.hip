@@ -442,11 +442,8 @@ static int launch_rt_owner(const lor_sched* s, int batch, const int32_t* elem_do
   const int MX = nex * P, MY = ney * P, MZ = nez * P;
   // tiles so that the last one reaches the last face: 7 (ntx - 1) + 7 >= MX
   const int ntx = static_cast<int>(ceil_div(MX, kRtStride)), nty = static_cast<int>(ceil_div(MY, kRtStride));
-  // Segments along z (a segment above the bottom integrates one extra layer
-  // to build its carry).  The waves run in rounds over the chip's wave slots
-  // (CUs x resident waves per CU, from the kernel's register use), so the
-  // launch takes about ceil(waves / slots) x (layers per wave + 1) layer
-  // steps: pick the segment length that minimises it.
+  // segments along z (one above the bottom integrates the layer below it too),
+  // over the wave slots that the kernel's register use gives
   static int wpc[64] = {};
   int dev = 0;
   LOR_HIP(hipGetDevice(&dev));
@@ -457,16 +454,7 @@ static int launch_rt_owner(const lor_sched* s, int batch, const int32_t* elem_do
   }
   const int64_t slots = static_cast<int64_t>(num_cus_rt()) * ((dev >= 0 && dev < 64) ? wpc[dev] : 1);
   const int64_t tiles = static_cast<int64_t>(ntx) * nty;
-  int64_t seglen = MZ, best = -1;
-  for (int64_t len = std::min<int64_t>(2, MZ); len <= MZ; ++len) {
-    const int64_t ns = ceil_div(MZ, len);
-    if (ns > 1 && ceil_div(MZ, ns) != len) continue;  // same split as a shorter length
-    const int64_t cost = ceil_div(tiles * ns * batch, slots) * (len + (ns > 1));
-    if (best < 0 || cost < best) {
-      best = cost;
-      seglen = len;
-    }
-  }
+  const int64_t seglen = march_segment(MZ, tiles * batch, slots, 1);
   const int nseg = static_cast<int>(ceil_div(MZ, seglen));
   dim3 grid(static_cast<unsigned>(ntx * nty), static_cast<unsigned>(nseg), static_cast<unsigned>(batch));
   k_rt_owner<P, T, R><<<grid, 64, 0, st>>>(nex, ney, nez, ntx, static_cast<int>(seglen), dev_at<int32_t>(s, s->off_elem3d), elem_dofs,
