@@ -100,12 +100,12 @@ __host__ __device__ __forceinline__ int64_t box_row_start(int64_t X, int64_t Y, 
 // are several (the layer below it, integrated again for its carry, and its
 // start).  The waves run in rounds over the chip's `slots` resident waves, so
 // a launch takes about ceil(waves / slots) x (length + extra) steps; the length
-// with the fewest is taken, so that neither the last round nor, on a small
+// with the fewest (*steps) is taken, so that neither the last round nor, on a small
 // mesh, the chip is left mostly idle.  `tiles`: waves per segment (all batch
 // entries).  Short segments are what a small mesh needs: H1 p = 2 on 4^3
 // elements (4 tiles) takes 48 us as segments of 8 layers and 11 us of 1 layer,
 // p = 5 on 13 x 9 x 11 47.7 us of 8 and 30.1 us of 4.
-inline int64_t march_segment(int64_t layers, int64_t tiles, int64_t slots, int64_t extra) {
+inline int64_t march_segment(int64_t layers, int64_t tiles, int64_t slots, int64_t extra, int64_t* steps = nullptr) {
   constexpr int64_t kMaxSegments = 65535;  // second grid dimension
   int64_t seglen = layers, best = -1;
   for (int64_t len = 1; len <= layers; ++len) {
@@ -118,6 +118,7 @@ inline int64_t march_segment(int64_t layers, int64_t tiles, int64_t slots, int64
       seglen = len;
     }
   }
+  if (steps) *steps = best;
   return seglen;
 }
 

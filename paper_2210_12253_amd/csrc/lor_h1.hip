@@ -446,9 +446,9 @@ static int dispatch_h1(int p, const lor_sched* s, int batch, const int32_t* ed, 
   }
 }
 
-template <typename T, typename R>
-int dispatch_owner(int p, const lor_sched* s, int batch, const int32_t* ed, const double* x, const void* k,
-                   double beta, const int32_t* rp, void* v, unsigned f, double thr, int32_t* diag, hipStream_t st);
+template <typename T>
+int dispatch_owner(int p, const lor_sched* s, int batch, const double* x, const void* k, double beta, void* v,
+                   unsigned f, double thr, int32_t* diag, hipStream_t st);
 bool owner_fits(const lor_sched* s, int tsize);
 
 // Shared argument checks of the value calls.
@@ -497,12 +497,10 @@ extern "C" int lor_assemble_h1(int p, int64_t nel, int64_t ndofs, int batch, con
                      ((flags & LOR_OWNER) || owner_fits(sched, dtype == LOR_F64 ? 8 : 4));
   const unsigned fb = flags & LOR_FP64_FALLBACK;
   if (dtype == LOR_F64)
-    return owner ? dispatch_owner<double, double>(p, sched, batch, elem_dofs, coords, kappa, beta, row_ptr, values,
-                                                  0u, det_ratio_thresh, diag, st)
+    return owner ? dispatch_owner<double>(p, sched, batch, coords, kappa, beta, values, 0u, det_ratio_thresh, diag, st)
                  : dispatch_h1<double, double>(p, sched, batch, elem_dofs, coords, kappa, beta, row_ptr, values, 0u,
                                                det_ratio_thresh, diag, st);
-  return owner ? dispatch_owner<float, float>(p, sched, batch, elem_dofs, coords, kappa, beta, row_ptr, values, fb,
-                                              det_ratio_thresh, diag, st)
+  return owner ? dispatch_owner<float>(p, sched, batch, coords, kappa, beta, values, fb, det_ratio_thresh, diag, st)
                : dispatch_h1<float, float>(p, sched, batch, elem_dofs, coords, kappa, beta, row_ptr, values, fb,
                                            det_ratio_thresh, diag, st);
 }

@@ -9,19 +9,21 @@
 // box_row_start(X, Y, Z), and cell (X, Y, Z) belongs to element
 // elem3d(X / p, Y / p, Z / p) at local subelement (X % p, Y % p, Z % p)):
 //
-//   * one wave = one worker, no workgroup barriers.  It takes a tile of 8 x 8
-//     cells in x and y (tiles overlap by one cell layer, stride 7) and marches
-//     along z over a segment of cell layers, one layer per step;
+//   * a workgroup takes a tile of S x S cells in x and y, one lane per cell
+//     (tiles overlap by one cell layer, stride S - 1), and marches along z over
+//     a segment of cell layers, one layer per step: S = 8, one wave without
+//     barriers, or S = 16, four waves that meet at barriers;
 //   * each lane integrates one cell of the layer (one Q1 cell matrix, 36
-//     unique entries) into the wave's LDS slab;
+//     unique entries) into the tile's LDS slab;
 //   * the rows of the layer's lower lattice plane are finished in registers:
 //     lane (x, y) sums, for row (x0 + x, y0 + y), the cells at the four
-//     lanes (x - a, y - b), corners c = 1 (the layer below, carried in
-//     registers from the previous step) before c = 0; the c = 1 corners of
-//     this layer are the carry into the next plane.  Rows x, y in [1, 7] of a
-//     tile are its own (also 0 on the box's lower faces), so the last cell
-//     column and row of a tile are integrated twice (by this tile and its
-//     neighbour): 64 cells per 49 rows;
+//     lanes (x - a, y - b), its own from registers, the others from the slab,
+//     corners c = 1 (the layer below, carried in registers from the previous
+//     step) before c = 0; the c = 1 corners of this layer are the carry into the
+//     next plane.  Rows x, y in [1, S - 1] of a tile are its own (also 0 on the
+//     box's lower faces), so the last cell column and row of a tile are
+//     integrated twice (by this tile and its neighbour): 64 cells per 49 rows at
+//     S = 8, 256 per 225 at S = 16;
 //   * the finished rows of each x-line are consecutive rows of the matrix;
 //     they are staged in LDS and stored as one contiguous span per line, with
 //     a fixed number of (predicated) store instructions per step: with a
@@ -39,62 +41,83 @@
 // same code).  The matrix is therefore bitwise symmetric and deterministic.
 // All sums are FP64, in the FP32 form too (each finished entry is rounded
 // once).
+//
+// What bounds it: instruction issue.  Per cell and step about 1,140 vector
+// instructions (940 of them the integration, lor_h1_math.hpp), four cycles
+// each, fill 64 to 70% of the SIMD's cycles at two waves per SIMD, LDS accesses
+// 40 to 50% of the CU's; HBM traffic is within 5% of the bytes that have to
+// move.  At p = 6 on 32^3 elements (192 M entries), same card: one wave per
+// SIMD with the entries from factor tables 806 us in FP64, 511 us in FP32; the
+// integration from moments and two waves per SIMD 580 and 488 us; edge vectors
+// formed once for the fallback test in FP32 454 us; tiles of 16 x 16 cells 556
+// and 423 us; own cell from registers 545 us (3.4 TB/s of the 1,840 MB) and 419
+// us (2.5 TB/s of 1,043 MB).  Three waves per SIMD in FP32 (168 registers) spill
+// and are slower (438 us).
 #include "lor_common.hpp"
 #include "lor_h1_math.hpp"
 
 namespace lor {
 
-constexpr int kOwnTile = 8;                  // cells per tile side (one wave: 8 x 8)
-constexpr int kOwnStride = kOwnTile - 1;     // tiles overlap by one cell
-constexpr int kOwnPts = (kOwnTile + 1) * (kOwnTile + 1);  // lattice points of one tile plane
-
-// LDS slab of one wave and waves per SIMD.  The FP64 form runs one wave per
-// SIMD: its integration wants ~250 VGPRs and the carry 36 more.  At two waves
-// per SIMD it spills about 30 registers; measured at the headline size that
-// was within 2% in time but wrote 15% more to HBM (the spills).  The FP32
-// form runs two waves per SIMD.
-template <typename T, typename R>
+// Tile of S x S cells, worked on by S * S / 64 waves (one lane per cell), and
+// its LDS: the cell matrices, [pair][lane], later the finished rows of the plane
+// staged per x-line, and two lattice planes (FP64 points).
+//   * FP64: that would be 22 KB per wave and hold the CU to 7 waves; but plane Z
+//     is not read again once the cells of layer Z have their corners, so the
+//     even planes take the first PLANE bytes, the odd ones the last, and the
+//     slab of layer Z everything but plane Z + 1: 20 KB per wave, 8 waves per CU
+//     (two per SIMD).
+//   * FP32 (which reads plane Z again in its fallback): slab, then both planes,
+//     13 KB per wave.
+template <typename T, typename R, int S>
 struct OwnCfg {
-  static constexpr int LPS = 1;   // cell layers per step
-  static constexpr int NPL = LPS + 1;  // lattice planes in LDS (ring)
-  static constexpr int WPE = sizeof(R) == 8 ? 1 : 2;  // waves per SIMD (second __launch_bounds__ argument)
-  // cell matrices [pair][lane]; once the row sums have read them, the finished
-  // rows of the plane staged per x-line
-  static constexpr int CELLS = 36 * 64 * static_cast<int>(sizeof(R));
-  static constexpr int ROWS = 64 * 27 * static_cast<int>(sizeof(T));
+  static_assert(S == 8 || S == 16, "one wave or four");
+  static constexpr int STRIDE = S - 1;      // tiles overlap by one cell
+  static constexpr int THREADS = S * S;
+  static constexpr int PTS = (S + 1) * (S + 1);  // lattice points of one tile plane
+  static constexpr bool ALIAS = sizeof(R) == 8;
+  static constexpr int WPE = 2;  // waves per SIMD (second __launch_bounds__ argument)
+  static constexpr int CELLS = 36 * THREADS * static_cast<int>(sizeof(R));
+  static constexpr int ROWS = 27 * THREADS * static_cast<int>(sizeof(T));
   static constexpr int SLAB = CELLS > ROWS ? CELLS : ROWS;
-  // one staged lattice plane (FP64 points), rounded to 16 bytes
-  static constexpr int PLANE = ((kOwnTile + 1) * (kOwnTile + 1) * 3 * 8 + 15) / 16 * 16;
-  // One buffer per wave: the slab at [0, SLAB), then the two planes (even Z,
-  // odd Z).
-  static constexpr int LDS = SLAB + 2 * PLANE;  // bytes per wave
-  // resident waves per CU: registers allow 4 WPE, LDS (160 KB) may allow fewer
-  static constexpr int WPC = 4 * WPE < 160 * 1024 / LDS ? 4 * WPE : 160 * 1024 / LDS;
+  static constexpr int PLANE = (PTS * 3 * 8 + 15) / 16 * 16;
+  static constexpr int LDS = SLAB + (ALIAS ? 1 : 2) * PLANE;
+  static constexpr int EVEN = ALIAS ? 0 : SLAB, ODD = ALIAS ? SLAB : SLAB + PLANE;
+  static constexpr int SLOTS = 4 * WPE * 64 / THREADS;  // resident workgroups per CU
+  static_assert(SLOTS * LDS <= 160 * 1024, "LDS for every wave slot");
+  // most entries of one x-line's span (S rows of 2 or 3 x-offsets, times 3 x 3),
+  // the store instructions per lane that cover it, and the lines of one wave
+  static constexpr int SPAN = (2 + 3 * (S - 1)) * 9;
+  static constexpr int ITERS = (SPAN + 63) / 64;
+  static constexpr int LINES = S * 64 / THREADS;
+  // the waves of a tile meet at barriers; one wave alone needs none, only that
+  // the compiler keeps the order of its LDS accesses
+  static __device__ __forceinline__ void sync() {
+    if constexpr (THREADS == 64)
+      __builtin_amdgcn_wave_barrier();
+    else
+      lds_barrier();
+  }
 };
 
 // FP32 form, strongly curved cell: FP64 geometry and quadrature from the FP64
-// corner coordinates, entries rounded to FP32 (64 = distance between two
-// entries of a cell in the slab).  Kept out of line: the branch is rare, and
-// inlined its FP64 registers would be reserved for the whole kernel.
-__device__ __noinline__ bool own_fp64_fallback(const double* __restrict__ pz0, const double* __restrict__ pz1,
-                                               int lx, int ly, double kap, double bet, float* out) {
-  double X[8][3];
+// corner coordinates, entries rounded to FP32.  pz0, pz1: the cell's first
+// corner in the planes below and above.  Kept out of line: the branch is rare,
+// and inlined its FP64 registers would be reserved for the whole kernel.
+template <int S>
+static __device__ __noinline__ bool own_fp64_fallback(const double* __restrict__ pz0, const double* __restrict__ pz1,
+                                               double kap, double bet, float* out) {
+  double ex[2][2][3], ey[2][2][3], ez[2][2][3];
+  {
+    double X[8][3];
 #pragma unroll
-  for (int v = 0; v < 8; ++v) {
-    const double* pl = (v >> 2) ? pz1 : pz0;
-    const int pidx = (lx + (v & 1)) + (kOwnTile + 1) * (ly + ((v >> 1) & 1));
+    for (int v = 0; v < 8; ++v) {
+      const double* pl = ((v >> 2) ? pz1 : pz0) + 3 * ((v & 1) + (S + 1) * ((v >> 1) & 1));
 #pragma unroll
-    for (int d = 0; d < 3; ++d) X[v][d] = pl[3 * pidx + d];
+      for (int d = 0; d < 3; ++d) X[v][d] = pl[d];
+    }
+    h1_edges<double>(X, ex, ey, ez);
   }
-  double dx[2][2][3], dy[2][2][3], dz[2][2][3];
-  h1_edges<double>(X, dx, dy, dz);
-  H1Factors<double> F;
-  const bool ok = h1_factors<double>(dx, dy, dz, kap, bet, F);
-#pragma unroll
-  for (int u = 0; u < 8; ++u)
-#pragma unroll
-    for (int v = u; v < 8; ++v) out[pair_index(u, v) * 64] = static_cast<float>(h1_entry<double>(F, u, v));
-  return ok;
+  return h1_cell<double>(ex, ey, ez, kap, bet, [&](int k, double x) { out[k * S * S] = static_cast<float>(x); });
 }
 
 // Offset index (dx + 1) + 3 (dy + 1) + 9 (dz + 1) of the entry from corner u
@@ -115,11 +138,6 @@ __host__ __device__ constexpr bool own_first(int k, int v, int up) {
       if (own_off(k2 + 4 * up, v2) == o) return false;
   return up == 1 || o >= 18;
 }
-
-// Most entries of one x-line's span (8 rows of 2 or 3 x-offsets, times 3 x 3),
-// and the store instructions per lane that cover it.
-constexpr int kOwnSpanMax = (2 + 3 * (kOwnTile - 1)) * 9;
-constexpr int kOwnSpanIters = (kOwnSpanMax + 63) / 64;
 
 // Memory is accessed through buffer resources (base, byte range): an access
 // outside the range reads 0 or is dropped, so every load and store is issued
@@ -162,30 +180,27 @@ __device__ __forceinline__ int own_xcd_tile(int b, int n) {
   return x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
 }
 
-template <int P, typename T, typename R>
-__global__ __launch_bounds__(64, (OwnCfg<T, R>::WPE)) void k_h1_owner(
+template <int P, typename T, typename R, int S>
+__global__ __launch_bounds__((OwnCfg<T, R, S>::THREADS), (OwnCfg<T, R, S>::WPE)) void k_h1_owner(
     int nex, int ney, int nez, int ntx, int seglen, const int32_t* __restrict__ elem3d,
     const double* __restrict__ coords, const T* __restrict__ kappa, T beta, int64_t nel, int64_t nnz,
     T* __restrict__ values, unsigned flags, R det_thresh, int32_t* __restrict__ diag) {
-  using C = OwnCfg<T, R>;
-  constexpr int NSUB = P * P * P, NPL = C::NPL;
-  static_assert(C::LPS == 1, "one cell layer per step");
-  static_assert(NPL == 2, "two staged planes");
+  using C = OwnCfg<T, R, S>;
+  constexpr int NSUB = P * P * P, PTS = C::PTS;
   __shared__ __align__(16) unsigned char sBuf[C::LDS];
-  auto plane = [&](int Z) { return reinterpret_cast<double*>(sBuf + C::SLAB + (Z & 1) * C::PLANE); };
-  R* const sCell = reinterpret_cast<R*>(sBuf);  // cell matrices of the layer
-  T* const sStg = reinterpret_cast<T*>(sBuf);   // then the finished rows of its lower plane
+  auto plane = [&](int Z) { return reinterpret_cast<double*>(sBuf + ((Z & 1) ? C::ODD : C::EVEN)); };
 
   const int NXc = nex * P, NYc = ney * P, NZc = nez * P;  // cells per axis
   const int LX = NXc + 1, LY = NYc + 1, LZ = NZc + 1;     // lattice points per axis
-  const int lane = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = C::THREADS == 64 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
   // Workgroups are dealt to the 8 XCDs in turn (workgroup b to XCD b mod 8),
   // each with its own L2; tiles next to each other share a column or row of
   // lattice points.  So XCD k gets a contiguous run of tiles (about an eighth
   // of the tile rows) instead of every eighth tile.
   const int tile = own_xcd_tile(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
   const int ti = tile % ntx, tj = tile / ntx;
-  const int x0 = kOwnStride * ti, y0 = kOwnStride * tj;
+  const int x0 = C::STRIDE * ti, y0 = C::STRIDE * tj;
   const int zs = blockIdx.y * seglen;
   const int ze = zs + seglen < NZc ? zs + seglen : NZc;
   kappa += static_cast<int64_t>(blockIdx.z) * nel * NSUB;
@@ -195,7 +210,7 @@ __global__ __launch_bounds__(64, (OwnCfg<T, R>::WPE)) void k_h1_owner(
   const auto rK = own_rsrc(kappa, static_cast<uint32_t>(nel * NSUB * static_cast<int64_t>(sizeof(T))));
   const auto rE = own_rsrc(elem3d, static_cast<uint32_t>(nel * 4));
 
-  const int lx = lane & 7, ly = lane >> 3;
+  const int lx = tid % S, ly = tid / S;
   const int cX = x0 + lx, cY = y0 + ly;                // this lane's cell / row column (x, y)
   const bool cell_in = cX < NXc && cY < NYc;
   const bool row_in = cX <= NXc && cY <= NYc;           // row (cX, cY) exists in every plane
@@ -206,13 +221,13 @@ __global__ __launch_bounds__(64, (OwnCfg<T, R>::WPE)) void k_h1_owner(
   // conditions: the row sums read all four cells (lanes x = 0 or y = 0 read
   // clamped cells and own no row), each owned row is one 27-entry copy, and
   // the seven owned lines of the plane are 7 rows x 27 entries each.
-  const bool tile_inner = ti > 0 && tj > 0 && x0 + kOwnTile <= NXc && y0 + kOwnTile <= NYc;
-  // lattice points of a plane: slot j -> point lane + 64 j of the 9 x 9 grid
+  const bool tile_inner = ti > 0 && tj > 0 && x0 + S <= NXc && y0 + S <= NYc;
+  // lattice points of a plane: slot j -> point tid + THREADS j of the (S + 1) x (S + 1) grid
   auto pt_xy = [&](int j, int& X, int& Y) {
-    const int pidx = lane + 64 * j;
-    X = x0 + pidx % (kOwnTile + 1);
-    Y = y0 + pidx / (kOwnTile + 1);
-    return pidx < kOwnPts && X <= NXc && Y <= NYc;
+    const int pidx = tid + C::THREADS * j;
+    X = x0 + pidx % (S + 1);
+    Y = y0 + pidx / (S + 1);
+    return pidx < PTS && X <= NXc && Y <= NYc;
   };
   // coordinates of the tile's points of plane Z (vertex X + LX (Y + LY Z));
   // absent points read 0 and are never used
@@ -234,8 +249,8 @@ __global__ __launch_bounds__(64, (OwnCfg<T, R>::WPE)) void k_h1_owner(
     double* pl = plane(Z);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int pidx = lane + 64 * j;
-      if (pidx < kOwnPts) {
+      const int pidx = tid + C::THREADS * j;
+      if (pidx < PTS) {
         pl[3 * pidx + 0] = xq[j][0];
         pl[3 * pidx + 1] = xq[j][1];
         pl[3 * pidx + 2] = xq[j][2];
@@ -287,7 +302,7 @@ __global__ __launch_bounds__(64, (OwnCfg<T, R>::WPE)) void k_h1_owner(
     // at the loop head (merged over both ways in) need not drain the prefetches
     const auto rNone = own_rsrc(values, 0u);
 #pragma unroll
-    for (int i = 0; i < 8 * kOwnSpanIters; ++i)  // distinct offsets, so that none is merged away
+    for (int i = 0; i < C::LINES * C::ITERS; ++i)  // distinct offsets, so that none is merged away
       own_st(T(0), rNone, static_cast<uint32_t>((64 * i + lane) * sizeof(T)));
   }
 
@@ -296,67 +311,70 @@ __global__ __launch_bounds__(64, (OwnCfg<T, R>::WPE)) void k_h1_owner(
   for (int o = 0; o < 18; ++o) carry[o] = 0.0;
 
   for (int Z = zfirst; Z < zend; ++Z) {
+    // the slab of this layer: its cell matrices, then the finished rows of its
+    // lower plane
+    unsigned char* const slab = sBuf + (C::ALIAS && (Z & 1) ? C::PLANE : 0);
+    R* const sCell = reinterpret_cast<R*>(slab);
+    T* const sStg = reinterpret_cast<T*>(slab);
+    C::sync();  // the rows of the step before are read; plane Z + 1 may lie there
     stage_plane(Z + 1, xq);
     load_xyz(Z + 2, xq);
-    __builtin_amdgcn_wave_barrier();
+    C::sync();
 
-    // the cell (cX, cY, Z): its 36 entries into the slab
-    if (cell_in && Z < NZc) {
-      const double* pz0 = plane(Z);
-      const double* pz1 = plane(Z + 1);
-      R* out = sCell + lane;
-      auto load_X = [&](double (&X)[8][3]) {
+    // the cell's own row corner: pairs (0, v) and (4, v), not read back from LDS
+    R keep[36];
+    // the cell (cX, cY, Z): its 36 entries into the slab (lanes without a cell
+    // integrate a cell of zeros that no row reads)
+    if (Z < NZc) {
+      const int corner = 3 * (lx + (S + 1) * ly);
+      const double* pz0 = plane(Z) + corner;
+      const double* pz1 = plane(Z + 1) + corner;
+      R ex[2][2][3], ey[2][2][3], ez[2][2][3];
+      {
+        double X[8][3];
 #pragma unroll
         for (int v = 0; v < 8; ++v) {
-          const double* pl = (v >> 2) ? pz1 : pz0;
-          const int pidx = (lx + (v & 1)) + (kOwnTile + 1) * (ly + ((v >> 1) & 1));
+          const double* pl = ((v >> 2) ? pz1 : pz0) + 3 * ((v & 1) + (S + 1) * ((v >> 1) & 1));
 #pragma unroll
-          for (int d = 0; d < 3; ++d) X[v][d] = pl[3 * pidx + d];
+          for (int d = 0; d < 3; ++d) X[v][d] = pl[d];
         }
-      };
-      const R kap = static_cast<R>(kq);
-      // counted once: a cell in a tile's last column (row) is also the first
-      // column (row) of the next tile, which counts it
-      const bool own = Z >= zs && lx < kOwnStride && ly < kOwnStride;
+        h1_edges<R>(X, ex, ey, ez);
+      }
+      if (C::ALIAS) C::sync();  // the slab takes the place of plane Z
       bool fallback = false;
       if constexpr (!std::is_same<R, double>::value) {
         if (flags & LOR_FP64_FALLBACK) {
-          R ex[2][2][3], ey[2][2][3], ez[2][2][3];
-          double X[8][3];
-          load_X(X);
-          h1_edges<R>(X, ex, ey, ez);
           R dmin, dmax;
           h1_corner_det_range<R>(ex, ey, ez, dmin, dmax);
-          fallback = !(dmin > R(0)) || dmax > det_thresh * dmin;
+          fallback = cell_in && (!(dmin > R(0)) || dmax > det_thresh * dmin);
         }
       }
-      if (!fallback) {
-        R ex[2][2][3], ey[2][2][3], ez[2][2][3];
-        {
-          double X[8][3];
-          load_X(X);
-          h1_edges<R>(X, ex, ey, ez);
-        }
-        H1Factors<R> F;
-        const bool ok = h1_factors<R>(ex, ey, ez, kap, static_cast<R>(beta), F);
+      // counted once: a cell in a tile's last column (row) is also the first
+      // column (row) of the next tile, which counts it
+      const bool counts = diag && cell_in && Z >= zs && lx < C::STRIDE && ly < C::STRIDE;
+      R* out = sCell + tid;
+      bool ok = h1_cell<R>(ex, ey, ez, static_cast<R>(kq), static_cast<R>(beta),
+                           [&](int k, R x) {
+                             keep[k] = x;
+                             if (k != pair_index(0, 0) && k != pair_index(0, 4) && k != pair_index(4, 4))
+                               out[k * C::THREADS] = x;
+                           });
+      if constexpr (!std::is_same<R, double>::value) {
+        if (fallback) {  // its entries again, in FP64
+          ok = own_fp64_fallback<S>(pz0, pz1, static_cast<double>(kq), static_cast<double>(beta), out);
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-#pragma unroll
-          for (int v = u; v < 8; ++v) out[pair_index(u, v) * 64] = h1_entry<R>(F, u, v);
-        if (!ok && own && diag) atomicAdd(&diag[1], 1);
-      } else {
-        // FP32 only: FP64 geometry, written to the slab
-        const bool ok = own_fp64_fallback(pz0, pz1, lx, ly, static_cast<double>(kap), static_cast<double>(beta),
-                                          reinterpret_cast<float*>(out));
-        if (own && diag) {
-          atomicAdd(&diag[0], 1);
-          if (!ok) atomicAdd(&diag[1], 1);
+          for (int v = 0; v < 8; ++v) {
+            keep[pair_index(0, v)] = out[pair_index(0, v) * C::THREADS];
+            keep[pair_index(4, v)] = out[pair_index(4, v) * C::THREADS];
+          }
+          if (counts) atomicAdd(&diag[0], 1);
         }
       }
+      if (counts && !ok) atomicAdd(&diag[1], 1);
     }
     kq = load_kap(Z + 1, el);
     el = load_elem(Z + 2);
-    __builtin_amdgcn_wave_barrier();
+    C::sync();
 
     // row (cX, cY) of plane Z: the carry (c = 1 corners, layer Z - 1) + this
     // layer's c = 0 corners; this layer's c = 1 corners are the next carry
@@ -372,11 +390,11 @@ __global__ __launch_bounds__(64, (OwnCfg<T, R>::WPE)) void k_h1_owner(
       R w[2][16];
       auto fetch = [&](int k, R(&wk)[16]) {
         const int a = k & 1, b = k >> 1;
-        const R* cm = sCell + (lx > a ? lx - a : 0) + 8 * (ly > b ? ly - b : 0);
+        const R* cm = sCell + (lx > a ? lx - a : 0) + S * (ly > b ? ly - b : 0);
 #pragma unroll
         for (int v = 0; v < 8; ++v) {
-          wk[v] = cm[pair_index(k, v) * 64];
-          wk[8 + v] = cm[pair_index(k + 4, v) * 64];
+          wk[v] = cm[pair_index(k, v) * C::THREADS];
+          wk[8 + v] = cm[pair_index(k + 4, v) * C::THREADS];
         }
       };
       auto sum = [&](int k, const R(&wk)[16]) {
@@ -384,15 +402,21 @@ __global__ __launch_bounds__(64, (OwnCfg<T, R>::WPE)) void k_h1_owner(
         for (int v = 0; v < 8; ++v) {
           double& ea = acc[own_off(k, v)];
           double& ec = carry[own_off(k + 4, v)];
-          ea = own_first(k, v, 0) ? static_cast<double>(wk[v]) : ea + static_cast<double>(wk[v]);
-          ec = own_first(k, v, 1) ? static_cast<double>(wk[8 + v]) : ec + static_cast<double>(wk[8 + v]);
+          const double ta = static_cast<double>(wk[v]), tc = static_cast<double>(wk[8 + v]);
+          ea = own_first(k, v, 0) ? ta : ea + ta;
+          ec = own_first(k, v, 1) ? tc : ec + tc;
         }
       };
-      fetch(0, w[0]);
       fetch(1, w[1]);
-      __builtin_amdgcn_sched_barrier(0);
-      sum(0, w[0]);
       fetch(2, w[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      R own[16];
+#pragma unroll
+      for (int v = 0; v < 8; ++v) {
+        own[v] = keep[pair_index(0, v)];
+        own[8 + v] = keep[pair_index(4, v)];
+      }
+      sum(0, own);
       __builtin_amdgcn_sched_barrier(0);
       sum(1, w[1]);
       fetch(3, w[1]);
@@ -406,17 +430,19 @@ __global__ __launch_bounds__(64, (OwnCfg<T, R>::WPE)) void k_h1_owner(
         for (int a = 0; a < 2; ++a) {
           const int sx = lx - a, sy = ly - b;
           if (sx >= 0 && sy >= 0 && x0 + sx < NXc && y0 + sy < NYc) {
-            const R* cm = sCell + sx + 8 * sy;
+            const R* cm = sCell + sx + S * sy;
             const int u0 = a + 2 * b, u1 = a + 2 * b + 4;
 #pragma unroll
             for (int v = 0; v < 8; ++v) {
-              acc[own_off(u0, v)] += static_cast<double>(cm[pair_index(u0, v) * 64]);
-              carry[own_off(u1, v)] += static_cast<double>(cm[pair_index(u1, v) * 64]);
+              const bool own = a == 0 && b == 0;
+              const int k0 = pair_index(u0, v), k1 = pair_index(u1, v);
+              acc[own_off(u0, v)] += static_cast<double>(own ? keep[k0] : cm[k0 * C::THREADS]);
+              carry[own_off(u1, v)] += static_cast<double>(own ? keep[k1] : cm[k1 * C::THREADS]);
             }
           }
         }
     }
-    __builtin_amdgcn_wave_barrier();
+    C::sync();
     if (Z < zs) continue;  // the layer below the segment: carry only
 
     // stage the owned rows of each x-line in CSR order: a row holds
@@ -429,7 +455,7 @@ __global__ __launch_bounds__(64, (OwnCfg<T, R>::WPE)) void k_h1_owner(
     const int pxa = static_cast<int>(box_prefix(xa, LX));
     if (fast) {
       if (lx > 0 && ly > 0) {
-        T* row = sStg + 27 * 8 * ly + 27 * (lx - 1);
+        T* row = sStg + 27 * S * ly + 27 * (lx - 1);
 #pragma unroll
         for (int k = 0; k < 27; ++k) row[k] = static_cast<T>(acc[k]);
       }
@@ -437,7 +463,7 @@ __global__ __launch_bounds__(64, (OwnCfg<T, R>::WPE)) void k_h1_owner(
       const int xlo = cX > 0, xhi = cX < NXc, nx = 1 + xlo + xhi;
       // x-offset counts of the owned rows before this one in its line
       const int before = static_cast<int>(box_prefix(cX, LX)) - pxa;
-      T* row = sStg + 27 * 8 * ly + before * nyz + (zlo * ny + ylo) * nx + xlo;
+      T* row = sStg + 27 * S * ly + before * nyz + (zlo * ny + ylo) * nx + xlo;
 #pragma unroll
       for (int dz = -1; dz <= 1; ++dz)
 #pragma unroll
@@ -449,7 +475,7 @@ __global__ __launch_bounds__(64, (OwnCfg<T, R>::WPE)) void k_h1_owner(
             if (ok) row[dz * nx * ny + dy * nx + dx] = static_cast<T>(acc[(dx + 1) + 3 * (dy + 1) + 9 * (dz + 1)]);
           }
     }
-    __builtin_amdgcn_wave_barrier();
+    C::sync();
     // one contiguous span per owned x-line, through a buffer resource over
     // exactly that span (empty for the lines the tile does not own).  Row
     // starts are below nnz < 2^31; line Y of plane Z starts at lb and its
@@ -457,46 +483,46 @@ __global__ __launch_bounds__(64, (OwnCfg<T, R>::WPE)) void k_h1_owner(
     // SX cy cz later
     const int SX = 3 * LX - 2;
     if (fast) {
-      // lines 1..7: 7 rows x 27 entries, the owned rows of line y0 + l from
+      // S - 1 rows x 27 entries per line, the owned rows of line y0 + l from
       // box_row_start(0, y0, Z) + 9 (SX l + box_prefix(xa)); line 0 empty
       const T* vb = values + (static_cast<int>(box_row_start(0, y0, Z, LX, LY, LZ)) + 9 * pxa);
       const int dl = 9 * SX;
-      // all of the plane's staged values first, then the stores
-      T sv[8][kOwnSpanIters];
+      // all of the wave's staged values first, then the stores
+      T sv[C::LINES][C::ITERS];
 #pragma unroll
-      for (int l = 0; l < 8; ++l)
+      for (int k = 0; k < C::LINES; ++k)
 #pragma unroll
-        for (int it = 0; it < kOwnSpanIters; ++it) {
+        for (int it = 0; it < C::ITERS; ++it) {
           const int t = lane + 64 * it;
-          sv[l][it] = sStg[27 * 8 * l + (t < kOwnSpanMax ? t : kOwnSpanMax - 1)];
+          sv[k][it] = sStg[27 * S * (k + C::LINES * wave) + (t < C::SPAN ? t : C::SPAN - 1)];
         }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int l = 0; l < 8; ++l) {
-        const auto rV = own_rsrc(vb + l * dl, l > 0 ? 7 * 27 * static_cast<uint32_t>(sizeof(T)) : 0u);
+      for (int k = 0; k < C::LINES; ++k) {
+        const int l = k + C::LINES * wave;
+        const auto rV = own_rsrc(vb + l * dl, l > 0 ? C::STRIDE * 27 * static_cast<uint32_t>(sizeof(T)) : 0u);
 #pragma unroll
-        for (int it = 0; it < kOwnSpanIters; ++it)
-          own_st(sv[l][it], rV, static_cast<uint32_t>((lane + 64 * it) * sizeof(T)));
+        for (int it = 0; it < C::ITERS; ++it)
+          own_st(sv[k][it], rV, static_cast<uint32_t>((lane + 64 * it) * sizeof(T)));
       }
       continue;
     }
-    const int xlast = x0 + 7 < NXc ? x0 + 7 : NXc;  // last owned row of the lines
+    const int xlast = x0 + C::STRIDE < NXc ? x0 + C::STRIDE : NXc;  // last owned row of the lines
     const int span_x = static_cast<int>(box_prefix(xlast + 1, LX)) - pxa;
     const int cz = 1 + zlo + zhi;
-    int lb = static_cast<int>(box_row_start(0, y0, Z, LX, LY, LZ));
 #pragma unroll
-    for (int l = 0; l < 8; ++l) {
-      const int Y = y0 + l;
+    for (int k = 0; k < C::LINES; ++k) {
+      const int l = k + C::LINES * wave, Y = y0 + l;
       const int cyz = box_count(Y, LY) * cz;
       const bool line = (l > 0 || tj == 0) && Y <= NYc;
       const int span = line ? span_x * cyz : 0;
-      const auto rV = own_rsrc(values + (line ? lb + cyz * pxa : 0), static_cast<uint32_t>(span * sizeof(T)));
-      lb += SX * cyz;
-      const T* src = sStg + 27 * 8 * l;
+      const int lb = line ? static_cast<int>(box_row_start(0, Y, Z, LX, LY, LZ)) + cyz * pxa : 0;
+      const auto rV = own_rsrc(values + lb, static_cast<uint32_t>(span * sizeof(T)));
+      const T* src = sStg + 27 * S * l;
 #pragma unroll
-      for (int it = 0; it < kOwnSpanIters; ++it) {
+      for (int it = 0; it < C::ITERS; ++it) {
         const int t = lane + 64 * it;
-        own_st(src[t < kOwnSpanMax ? t : kOwnSpanMax - 1], rV, static_cast<uint32_t>(t * sizeof(T)));
+        own_st(src[t < C::SPAN ? t : C::SPAN - 1], rV, static_cast<uint32_t>(t * sizeof(T)));
       }
     }
   }
@@ -523,28 +549,21 @@ static int owner_num_cus() {
   return cus[dev];
 }
 
-template <int P, typename T, typename R>
-static int launch_owner(const lor_sched* sched, int batch, const void* kappa, double beta, const double* coords,
-                        const int32_t* row_ptr, void* values, unsigned flags, double thr, int32_t* diag,
-                        hipStream_t st) {
+template <int P, typename T, typename R, int S>
+static int launch_owner_tile(const lor_sched* sched, int batch, const void* kappa, double beta, const double* coords,
+                             void* values, unsigned flags, double thr, int32_t* diag, hipStream_t st) {
+  using C = OwnCfg<T, R, S>;
   const int nex = sched->box[0], ney = sched->box[1], nez = sched->box[2];
-  if (nex < 1 || ney < 1 || nez < 1 || static_cast<int64_t>(nex) * ney * nez != sched->nel ||
-      (static_cast<int64_t>(nex) * P + 1) * (static_cast<int64_t>(ney) * P + 1) * (static_cast<int64_t>(nez) * P + 1) !=
-          sched->nrows)
-    LOR_FAIL(LOR_EINVAL, "the owner-computes schedule does not describe the mesh");
-  if (!owner_fits(sched, static_cast<int>(sizeof(T))))
-    LOR_FAIL(LOR_EUNSUPPORTED, "owner-computes kernel: coordinates or coefficients span 4 GiB or more");
   const int NXc = nex * P, NYc = ney * P, NZc = nez * P;
-  const int64_t ntx = ceil_div(NXc, kOwnStride), nty = ceil_div(NYc, kOwnStride);
+  const int64_t ntx = ceil_div(NXc, C::STRIDE), nty = ceil_div(NYc, C::STRIDE);
   const int64_t tiles = ntx * nty;
   if (tiles > INT32_MAX) LOR_FAIL(LOR_EOVERFLOW, "too many owner-computes tiles");
   // segments along z: one above the bottom integrates the layer below it too
-  const int64_t slots = static_cast<int64_t>(owner_num_cus()) * OwnCfg<T, R>::WPC;
+  const int64_t slots = static_cast<int64_t>(owner_num_cus()) * C::SLOTS;
   const int64_t seglen = march_segment(NZc, tiles * batch, slots, 1);
   const int64_t nseg = ceil_div(NZc, seglen);
   dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>(nseg), static_cast<unsigned>(batch));
-  (void)row_ptr;  // the rows start where the lattice puts them (the pattern call checked row_ptr)
-  k_h1_owner<P, T, R><<<grid, 64, 0, st>>>(
+  k_h1_owner<P, T, R, S><<<grid, C::THREADS, 0, st>>>(
       nex, ney, nez, static_cast<int>(ntx), static_cast<int>(seglen), dev_at<int32_t>(sched, sched->off_elem3d),
       coords, static_cast<const T*>(kappa), static_cast<T>(beta), sched->nel, sched->nnz, static_cast<T*>(values),
       flags, static_cast<R>(thr), diag);
@@ -552,24 +571,53 @@ static int launch_owner(const lor_sched* sched, int batch, const void* kappa, do
   return LOR_OK;
 }
 
-template <typename T, typename R>
-int dispatch_owner(int p, const lor_sched* s, int batch, const int32_t* ed, const double* x, const void* k,
-                   double beta, const int32_t* rp, void* v, unsigned f, double thr, int32_t* diag, hipStream_t st) {
-  (void)ed;
+template <int P, typename T>
+static int launch_owner(const lor_sched* sched, int batch, const void* kappa, double beta, const double* coords,
+                        void* values, unsigned flags, double thr, int32_t* diag, hipStream_t st) {
+  const int nex = sched->box[0], ney = sched->box[1], nez = sched->box[2];
+  if (nex < 1 || ney < 1 || nez < 1 || static_cast<int64_t>(nex) * ney * nez != sched->nel ||
+      (static_cast<int64_t>(nex) * P + 1) * (static_cast<int64_t>(ney) * P + 1) * (static_cast<int64_t>(nez) * P + 1) !=
+          sched->nrows)
+    LOR_FAIL(LOR_EINVAL, "the owner-computes schedule does not describe the mesh");
+  if (!owner_fits(sched, static_cast<int>(sizeof(T))))
+    LOR_FAIL(LOR_EUNSUPPORTED, "owner-computes kernel: coordinates or coefficients span 4 GiB or more");
+  // The tile with fewer steps (rounds x layers per wave): on a large mesh 16 x 16,
+  // which integrates 1.14 cells per row instead of 1.31 (p = 6, 32^3: 65 steps
+  // against 80, 556 us against 583).  On equal numbers, as on small meshes, 8 x 8:
+  // its waves wait for no barrier (p = 5, 13 x 9 x 11: 25.4 us against 26.2).
+  const int64_t cus = owner_num_cus();
+  auto steps = [&](int64_t stride, int64_t slots) {
+    int64_t cost;
+    march_segment(static_cast<int64_t>(nez) * P, ceil_div(nex * P, stride) * ceil_div(ney * P, stride) * batch, slots, 1,
+                  &cost);
+    return cost;
+  };
+  using C8 = OwnCfg<T, T, 8>;
+  using C16 = OwnCfg<T, T, 16>;
+  if (steps(C16::STRIDE, cus * C16::SLOTS) < steps(C8::STRIDE, cus * C8::SLOTS))
+    return launch_owner_tile<P, T, T, 16>(sched, batch, kappa, beta, coords, values, flags, thr, diag, st);
+  return launch_owner_tile<P, T, T, 8>(sched, batch, kappa, beta, coords, values, flags, thr, diag, st);
+}
+
+// Values on a box lattice.  The rows start where the lattice puts them (the
+// pattern call checked row_ptr).
+template <typename T>
+int dispatch_owner(int p, const lor_sched* s, int batch, const double* x, const void* k, double beta, void* v,
+                   unsigned f, double thr, int32_t* diag, hipStream_t st) {
   switch (p) {
-    case 1: return launch_owner<1, T, R>(s, batch, k, beta, x, rp, v, f, thr, diag, st);
-    case 2: return launch_owner<2, T, R>(s, batch, k, beta, x, rp, v, f, thr, diag, st);
-    case 3: return launch_owner<3, T, R>(s, batch, k, beta, x, rp, v, f, thr, diag, st);
-    case 4: return launch_owner<4, T, R>(s, batch, k, beta, x, rp, v, f, thr, diag, st);
-    case 5: return launch_owner<5, T, R>(s, batch, k, beta, x, rp, v, f, thr, diag, st);
-    case 6: return launch_owner<6, T, R>(s, batch, k, beta, x, rp, v, f, thr, diag, st);
+    case 1: return launch_owner<1, T>(s, batch, k, beta, x, v, f, thr, diag, st);
+    case 2: return launch_owner<2, T>(s, batch, k, beta, x, v, f, thr, diag, st);
+    case 3: return launch_owner<3, T>(s, batch, k, beta, x, v, f, thr, diag, st);
+    case 4: return launch_owner<4, T>(s, batch, k, beta, x, v, f, thr, diag, st);
+    case 5: return launch_owner<5, T>(s, batch, k, beta, x, v, f, thr, diag, st);
+    case 6: return launch_owner<6, T>(s, batch, k, beta, x, v, f, thr, diag, st);
     default: LOR_FAIL(LOR_EUNSUPPORTED, "p = %d not compiled", p);
   }
 }
 
-template int dispatch_owner<double, double>(int, const lor_sched*, int, const int32_t*, const double*, const void*,
-                                            double, const int32_t*, void*, unsigned, double, int32_t*, hipStream_t);
-template int dispatch_owner<float, float>(int, const lor_sched*, int, const int32_t*, const double*, const void*,
-                                          double, const int32_t*, void*, unsigned, double, int32_t*, hipStream_t);
+template int dispatch_owner<double>(int, const lor_sched*, int, const double*, const void*, double, void*, unsigned,
+                                    double, int32_t*, hipStream_t);
+template int dispatch_owner<float>(int, const lor_sched*, int, const double*, const void*, double, void*, unsigned,
+                                   double, int32_t*, hipStream_t);
 
 }  // namespace lor
