@@ -36,10 +36,13 @@ struct H1Cfg {
   static constexpr int T1 = 3 * P + 1;             // stencil entries per axis
   static constexpr int NENT = T1 * T1 * T1;        // local stencil entries per element
   static constexpr int NENTP = (NENT + 15) / 16 * 16;  // table stride in bytes
-  // elements per group: 256 lanes cover the subelements and every lane owns
-  // at most two local rows
-  static constexpr int E = P == 1 ? 64 : P == 2 ? 16 : P == 3 ? 8 : P == 4 ? 4 : P == 5 ? 2 : 1;
-  static constexpr int THREADS = 256;
+  // Elements per group: the workgroup's lanes cover the subelements and every
+  // lane owns at most two local rows.  128 lanes where they do (p <= 5): with
+  // 256 and twice the elements, p = 3 to 5 held one workgroup per CU (88 to 98 KB
+  // of LDS in FP64), whose phases nothing overlapped; p = 5, 7,200 elements:
+  // 295 -> 214 us.
+  static constexpr int E = P == 1 ? 32 : P == 2 ? 8 : P == 3 ? 4 : P == 4 ? 2 : 1;
+  static constexpr int THREADS = P == 6 ? 256 : 128;
   static constexpr int RV = (E * NLOC + THREADS - 1) / THREADS;         // vertex slots per lane
   static constexpr int TW = E * NENTP / 4;                             // table words per group
   static constexpr int RW = (TW + THREADS - 1) / THREADS;              // table words per lane
@@ -51,9 +54,9 @@ struct H1Cfg {
 };
 
 // Resident workgroups per CU: as many as the LDS of one workgroup allows, up
-// to two in FP64 (the integration needs ~250 VGPRs per lane) and three in
-// FP32 (168 VGPRs per lane; the spills this costs are cheaper than the
-// latency a third workgroup hides).
+// to two waves per SIMD (256 registers per lane, no spills).  In FP32 three waves
+// per SIMD fit with 40 to 60 spilled registers and are slower (p = 6, 12,096
+// elements: 583 us against 468).
 template <int P, typename R>
 struct H1Occ {
   using C = H1Cfg<P>;
@@ -61,9 +64,10 @@ struct H1Occ {
   static constexpr int STGW = C::E * C::NENT;
   static constexpr int LDS = C::E * C::NLOC * 28 + C::E * C::NENTP +
                              (SUBW > STGW ? SUBW : STGW) * static_cast<int>(sizeof(R)) + 2 * C::MAXCHUNK * 4;
-  static constexpr int WANT = sizeof(R) == 8 ? 2 : 3;
+  static constexpr int WANT = 2 * 256 / C::THREADS;
   static constexpr int FIT = 160 * 1024 / LDS;
   static constexpr int WPC = WANT < FIT ? WANT : (FIT > 0 ? FIT : 1);
+  static constexpr int WPE = (WPC * C::THREADS / 64 + 3) / 4;  // waves per SIMD
 };
 
 // number of stencil offsets along one axis at lattice coordinate t, and the
@@ -83,22 +87,16 @@ template <int NSUB>
 __device__ __forceinline__ bool h1_fp64_fallback(const double (&X)[8][3], double kap, double bet, float* out) {
   double dx[2][2][3], dy[2][2][3], dz[2][2][3];
   h1_edges<double>(X, dx, dy, dz);
-  H1Factors<double> F;
-  const bool ok = h1_factors<double>(dx, dy, dz, kap, bet, F);
-#pragma unroll
-  for (int u = 0; u < 8; ++u)
-#pragma unroll
-    for (int v = u; v < 8; ++v) out[pair_index(u, v) * NSUB] = static_cast<float>(h1_entry<double>(F, u, v));
-  return ok;
+  return h1_cell<double>(dx, dy, dz, kap, bet, [&](int k, double x) { out[k * NSUB] = static_cast<float>(x); });
 }
 
 template <int P, typename T, typename R>
-__global__ __launch_bounds__(256, (H1Occ<P, R>::WPC)) void k_h1_assemble(
+__global__ __launch_bounds__(H1Cfg<P>::THREADS, (H1Occ<P, R>::WPE)) void k_h1_assemble(
     const int32_t* __restrict__ order, const int32_t* __restrict__ order_class, int32_t ncol, int32_t chunk,
     const int32_t* __restrict__ elem_dofs,
     const double* __restrict__ coords, const T* __restrict__ kappa, T beta, const int32_t* __restrict__ row_ptr,
     const uint8_t* __restrict__ tables, int64_t tab_stride, const uint16_t* __restrict__ ent_row, int64_t nel,
-    int64_t nnz, T* __restrict__ values, const T* __restrict__ zero, unsigned flags, R det_thresh,
+    int64_t nnz, T* __restrict__ values, unsigned flags, R det_thresh,
     int32_t* __restrict__ diag) {
   using C = H1Cfg<P>;
   constexpr int Q = C::Q, NSUB = C::NSUB, NLOC = C::NLOC, NENT = C::NENT, NENTP = C::NENTP, E = C::E;
@@ -122,9 +120,9 @@ __global__ __launch_bounds__(256, (H1Occ<P, R>::WPC)) void k_h1_assemble(
   const int64_t cbeg = static_cast<int64_t>(blockIdx.x) * chunk;
   const int nce = static_cast<int>(ncol - cbeg < chunk ? ncol - cbeg : chunk);
   const int ngr = (nce + E - 1) / E;
-  if (tid < nce) {
-    sOrd[tid] = order[cbeg + tid];
-    sCls[tid] = order_class[cbeg + tid];
+  for (int i = tid; i < nce; i += TH) {
+    sOrd[i] = order[cbeg + i];
+    sCls[i] = order_class[cbeg + i];
   }
   __syncthreads();
 
@@ -199,6 +197,18 @@ __global__ __launch_bounds__(256, (H1Occ<P, R>::WPC)) void k_h1_assemble(
     kq = load_kap(0);
   }
 
+  // local row of each of this lane's phase-3 entries, two to a register: the
+  // same for every group
+  uint32_t erow2[(NJ + 1) / 2];
+#pragma unroll
+  for (int j = 0; j < NJ; j += 2) {
+    auto row_of = [&](int jj) -> uint32_t {
+      const uint32_t i = static_cast<uint32_t>(tid + jj * TH);
+      return jj < NJ && i < static_cast<uint32_t>(E * NENT) ? ent_row[i % NENT] : 0u;
+    };
+    erow2[j / 2] = row_of(j) | row_of(j + 1) << 16;
+  }
+
   for (int g = 0; g < ngr; ++g) {
     const int ne = E == 1 ? 1 : group_size(g);
     // Index arithmetic below is cheap; an opaque copy of the lane id keeps the
@@ -258,12 +268,7 @@ __global__ __launch_bounds__(256, (H1Occ<P, R>::WPC)) void k_h1_assemble(
           load_X(X);
           h1_edges<R>(X, ex, ey, ez);
         }
-        H1Factors<R> F;
-        const bool ok = h1_factors<R>(ex, ey, ez, kap, static_cast<R>(beta), F);
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-#pragma unroll
-          for (int v = u; v < 8; ++v) out[pair_index(u, v) * NSUB] = h1_entry<R>(F, u, v);
+        const bool ok = h1_cell<R>(ex, ey, ez, kap, static_cast<R>(beta), [&](int k, R x) { out[k * NSUB] = x; });
         if (!ok && diag) atomicAdd(&diag[1], 1);
       }
       if (fallback) {
@@ -282,7 +287,7 @@ __global__ __launch_bounds__(256, (H1Occ<P, R>::WPC)) void k_h1_assemble(
     kq = load_kap(g + 1);  // the next group's coefficient, after this group's last use
     lds_barrier();
 
-    // phase 2: local rows.  Lane owns rows tid and tid + 256.  The rank table
+    // phase 2: local rows.  Lane owns rows tid and tid + TH.  The rank table
     // of the group is fetched meanwhile (needed in phase 3 only).
     uint32_t twq[RW];
     load_tab(g, twq);
@@ -347,21 +352,10 @@ __global__ __launch_bounds__(256, (H1Occ<P, R>::WPC)) void k_h1_assemble(
     lds_barrier();
 
     // phase 3: store into the CSR values.  Every load is issued before any
-    // store and the memory instructions sit in straight-line code (no branch
-    // per entry), so each store waits only for its own operand.  A first
-    // contributor reads its "old value" from a zero slot (one shared cache
-    // line) instead of taking a branch; lanes past the end of the group
-    // repeat their first store.
+    // store.  Only entries that are not first contributions load the stored
+    // value; lanes past the end of the group repeat their first store.
     if (tid < ne * NENT) {
       const uint32_t ut = static_cast<uint32_t>(tid);
-      uint32_t erow[NJ];
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const uint32_t i = ut + j * TH;
-        const bool ok = i < static_cast<uint32_t>(ne * NENT);
-        const uint32_t el = E == 1 ? 0u : i / NENT;
-        erow[j] = ent_row[ok ? i - el * NENT : 0u];
-      }
       uint32_t pos[NJ];
       T old[NJ];
 #pragma unroll
@@ -370,21 +364,26 @@ __global__ __launch_bounds__(256, (H1Occ<P, R>::WPC)) void k_h1_assemble(
         const bool ok = i < static_cast<uint32_t>(ne * NENT);
         const uint32_t el = ok ? (E == 1 ? 0u : i / NENT) : 0u;
         const uint32_t k = ok ? i - el * NENT : 0u;
+        const uint32_t er = ok ? (erow2[j / 2] >> (16 * (j & 1))) & 0xffffu : 0u;
         const uint32_t t = sTab[el * NENTP + k];
-        pos[j] = static_cast<uint32_t>(sRp[el * NLOC + erow[j]]) + (t & kRankMask);
-        old[j] = *((t & kFirstBit) ? zero : values + pos[j]);
+        pos[j] = static_cast<uint32_t>(sRp[el * NLOC + er]) + (t & kRankMask);
+        old[j] = T(0);
+        if (!(t & kFirstBit)) old[j] = values[pos[j]];
       }
-      // non-temporal stores: the values are not re-read by this launch (later
-      // colours read them back after the kernel boundary), and marking them
-      // streaming measured about 4% faster in FP64
+      // Ordinary stores, not streaming ones: the fragments that an element adds
+      // to a shared row lie in lines which other stores of the same launch and of
+      // later colours touch too, and L2 puts them together.  Triangle-split mesh,
+      // p = 6, 32,256 elements: 2.80 -> 2.19 GB written, 1,612 -> 1,297 us
+      // (1,810 MB have to move; the rest is rows on element faces written and
+      // read once per element, which is what bounds this kernel).
       const T v0 = sStg[ut] + old[0];
-      __builtin_nontemporal_store(v0, values + pos[0]);
+      values[pos[0]] = v0;
 #pragma unroll
       for (int j = 1; j < NJ; ++j) {
         const uint32_t i = ut + j * TH;
         const bool ok = i < static_cast<uint32_t>(ne * NENT);
         const T v = sStg[ok ? i : ut] + old[j];
-        __builtin_nontemporal_store(ok ? v : v0, values + (ok ? pos[j] : pos[0]));
+        values[ok ? pos[j] : pos[0]] = ok ? v : v0;
       }
     }
   }
@@ -425,7 +424,7 @@ static int launch_h1(const lor_sched* sched, int batch, const int32_t* elem_dofs
     k_h1_assemble<P, T, R><<<grid, C::THREADS, 0, st>>>(
         order + sched->color_ptr[c], ocls + sched->color_ptr[c], n, chunk, elem_dofs, coords, static_cast<const T*>(kappa), static_cast<T>(beta),
         row_ptr, tab, sched->tab_stride, ent_row, sched->nel, sched->nnz, static_cast<T*>(values),
-        dev_at<T>(sched, sched->off_zero), flags, static_cast<R>(thr), diag);
+        flags, static_cast<R>(thr), diag);
     LOR_LAUNCHED("k_h1_assemble");
   }
   return LOR_OK;
