@@ -188,8 +188,7 @@ __global__ __launch_bounds__(64, 2) void k_nd_owner(int nex, int ney, int nez, i
   constexpr int SLAB = RPP * 12 * 64 * static_cast<int>(sizeof(R));
   constexpr int STG = 64 * kNdRow * static_cast<int>(sizeof(T));
   __shared__ __align__(16) unsigned char sBuf[SLAB > STG ? SLAB : STG];
-  __shared__ int64_t sStart[64];
-  __shared__ int32_t sLen[64];
+  __shared__ int2 sRow[64];  // start and length of the row of each lane
   R* const sCell = reinterpret_cast<R*>(sBuf);  // the 4 rows along M of each cell: [row a + 2b][col][lane]
   T* const sStg = reinterpret_cast<T*>(sBuf);   // then the finished rows: [lane][kNdRow]
 
@@ -223,6 +222,14 @@ __global__ __launch_bounds__(64, 2) void k_nd_owner(int nex, int ney, int nez, i
   // first; only the x-edge launch counts
   const bool count = M == 0 && l1 < kNdStride && l2 < kNdStride;
 
+  // entry e of local edges r and v with the sign of their orientations
+  auto oriented = [](R e, unsigned negmask, int r, int v) -> R {
+    const uint32_t s = ((negmask << (31 - r)) ^ (negmask << (31 - v))) & 0x80000000u;
+    if constexpr (sizeof(R) == 8)
+      return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, e) ^ (static_cast<uint64_t>(s) << 32));
+    else
+      return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, e) ^ s);
+  };
   // the cell's rows RBASE + jb .. RBASE + jb + RPP - 1 into the slab, signed
   auto write_rows = [&](const H1Factors<R>& F, const NDCurl<R>& W, unsigned negmask, int jb) {
 #pragma unroll
@@ -231,7 +238,7 @@ __global__ __launch_bounds__(64, 2) void k_nd_owner(int nex, int ney, int nez, i
 #pragma unroll
       for (int v = 0; v < 12; ++v) {
         const R e = nd_entry<R>(F, W, r < v ? r : v, r < v ? v : r);
-        sCell[(jj * 12 + v) * 64 + lane] = (((negmask >> r) ^ (negmask >> v)) & 1u) ? -e : e;
+        sCell[(jj * 12 + v) * 64 + lane] = oriented(e, negmask, r, v);
       }
     }
   };
@@ -282,6 +289,15 @@ __global__ __launch_bounds__(64, 2) void k_nd_owner(int nex, int ney, int nez, i
 
   for (int cm = ms; cm < me; ++cm) {
     double acc[kNdRow];
+    // the start of this lane's row, needed last
+    int32_t start = 0;
+    if (row_own) {
+      int R3[3];
+      R3[M] = cm;
+      R3[T1] = c1;
+      R3[T2] = c2;
+      start = row_ptr[nd_edge_id(M, R3[0], R3[1], R3[2], L[0], L[1], L[2])];
+    }
     if constexpr (NH == 1) {
       // all 4 rows through the slab at once; in the FP32 form strongly
       // distorted cells take the FP64 fallback (the gathers written out here:
@@ -336,7 +352,7 @@ __global__ __launch_bounds__(64, 2) void k_nd_owner(int nex, int ney, int nez, i
 #pragma unroll
             for (int v = 0; v < 12; ++v) {
               const R e = nd_entry<R>(F, W, r < v ? r : v, r < v ? v : r);
-              sCell[(j * 12 + v) * 64 + lane] = (((negmask >> r) ^ (negmask >> v)) & 1u) ? -e : e;
+              sCell[(j * 12 + v) * 64 + lane] = oriented(e, negmask, r, v);
             }
           }
           if (!ok && count && diag) atomicAdd(&diag[1], 1);
@@ -350,7 +366,7 @@ __global__ __launch_bounds__(64, 2) void k_nd_owner(int nex, int ney, int nez, i
           }
         }
       }
-      __syncthreads();
+      __builtin_amdgcn_wave_barrier();
 
       // the row of the edge along M at (cm, c1, c2): the cells at lanes
       // (l1 - a, l2 - b) in increasing (z, y, x), i.e. b = 1 before b = 0 and a
@@ -369,7 +385,7 @@ __global__ __launch_bounds__(64, 2) void k_nd_owner(int nex, int ney, int nez, i
             }
           }
       }
-      __syncthreads();  // the staging area is the slab
+      __builtin_amdgcn_wave_barrier();  // the staging area is the slab
     } else {
       // FP64 form: the rows of b = 1 (local edges RBASE + 2, + 3), then those
       // of b = 0, each pass through the half-size slab
@@ -396,21 +412,16 @@ __global__ __launch_bounds__(64, 2) void k_nd_owner(int nex, int ney, int nez, i
 #pragma unroll
       for (int b = 1; b >= 0; --b) {
         if (cell_col) write_rows(F, W, negmask, 2 * b);
-        __syncthreads();
+        __builtin_amdgcn_wave_barrier();
         if (row_own) sum_rows(acc, b, b, 2 * b);
-        __syncthreads();  // the slab is written again, or is the staging area
+        __builtin_amdgcn_wave_barrier();  // the slab is written again, or is the staging area
       }
     }
 
     // stage the row, compacted on the box faces, and its start and length
+    int len = 0;
     if (row_own) {
-      int R3[3];
-      R3[M] = cm;
-      R3[T1] = c1;
-      R3[T2] = c2;
-      const int64_t row = nd_edge_id(M, R3[0], R3[1], R3[2], L[0], L[1], L[2]);
       T* dst = sStg + lane * kNdRow;
-      int len = 0;
       if (inside) {
 #pragma unroll
         for (int k = 0; k < kNdRow; ++k) dst[k] = static_cast<T>(acc[k]);
@@ -445,21 +456,21 @@ __global__ __launch_bounds__(64, 2) void k_nd_owner(int nex, int ney, int nez, i
           if (ok) dst[pos] = static_cast<T>(acc[k]);
         }
       }
-      sStart[lane] = static_cast<int64_t>(row_ptr[row]);
-      sLen[lane] = len;
-    } else {
-      sLen[lane] = 0;
     }
-    __syncthreads();
+    sRow[lane] = make_int2(start, len);
+    __builtin_amdgcn_wave_barrier();
     // rows one after another: entry t of the staging area is entry t % 33 of
-    // the row of lane t / 33
-#pragma unroll 4
+    // the row of lane t / 33, and 64 further on the row is 1 or 2 further
+    int r = lane / kNdRow, k = lane - r * kNdRow;
+#pragma unroll 11
     for (int it = 0; it < kNdStoreIters; ++it) {
-      const int t = lane + 64 * it;
-      const int r = t / kNdRow, k = t - r * kNdRow;
-      if (k < sLen[r]) values[sStart[r] + k] = sStg[t];
+      const int2 row = sRow[r];
+      if (k < row.y) values[static_cast<int64_t>(row.x) + k] = sStg[lane + 64 * it];
+      const bool wrap = k >= 2 * kNdRow - 64;
+      k += wrap ? 64 - 2 * kNdRow : 64 - kNdRow;
+      r += wrap ? 2 : 1;
     }
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
