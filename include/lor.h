@@ -73,10 +73,10 @@ typedef enum { LOR_DIAG_ONE = 0, LOR_DIAG_KEEP = 1, LOR_DIAG_ZERO = 2 } lor_diag
 #define LOR_FP64_FALLBACK 0x1u
 /* lor_assemble_h1, lor_assemble_h1_2d, lor_assemble_rt and lor_assemble_nd:
  * kernel choice.  By default the owner-computes kernel runs when the schedule
- * has it (sched->owner) and the coloured kernel otherwise; LOR_COLORED forces
- * the coloured kernel, LOR_OWNER the owner-computes one (LOR_EUNSUPPORTED if
- * the schedule has none).  Both give the same matrix up to the order of the
- * floating-point sums. */
+ * has it (sched->owner); otherwise a kernel that sums row by row on small meshes
+ * and the coloured kernel on large ones.  LOR_COLORED forces the coloured
+ * kernel, LOR_OWNER the owner-computes one (LOR_EUNSUPPORTED if the schedule has
+ * none).  All give the same matrix up to the order of the floating-point sums. */
 #define LOR_COLORED 0x2u
 #define LOR_OWNER 0x4u
 

@@ -343,6 +343,18 @@ __device__ __forceinline__ void scaled_columns(const R (&e)[2][2][3], R (&c)[2][
   }
 }
 
+// c x with the constant's rounding to R made up for (rounded once, it would be
+// the same relative error in every entry).
+template <typename R>
+__device__ __forceinline__ R scale_by(double c, R x) {
+  if constexpr (sizeof(R) == 8) {
+    return c * x;
+  } else {
+    const R hi = static_cast<R>(c), lo = static_cast<R>(c - static_cast<double>(hi));
+    return __builtin_fmaf(lo, x, hi * x);
+  }
+}
+
 // Entries of K + M of one cell from its edge vectors, entry (u, v), u <= v,
 // handed to st(pair_index(u, v), value).  Returns false if det J <= 0 at a
 // Gauss point.
@@ -354,8 +366,8 @@ __device__ __forceinline__ bool h1_cell(const R (&ex)[2][2][3], const R (&ey)[2]
   scaled_columns<R>(ey, c1);
   scaled_columns<R>(ez, c2);
   // columns are J / kGA2: det J = kGA2^3 det, r_a . r_b / det J = kGA2 (r_a . r_b / det)
-  const R wk = R(0.125 * kGA2 / 36.0) * kap;
-  const R wb = R(0.125 * kGA2 * kGA2 * kGA2 / 216.0) * bet;
+  const R wk = scale_by<R>(0.125 * kGA2 / 36.0, kap);
+  const R wb = scale_by<R>(0.125 * kGA2 * kGA2 * kGA2 / 216.0, bet);
   bool ok = true;
   // moments: xx[j][k], yy[i][k], zz[i][j]; xy, xz, yz, dd [i][j][k]
   R xx[2][2], yy[2][2], zz[2][2] = {}, xy[2][2][2], xz[2][2][2], yz[2][2][2], dd[2][2][2];

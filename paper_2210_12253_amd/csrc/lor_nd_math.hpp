@@ -47,8 +47,8 @@ __device__ __forceinline__ bool nd_factors(const R (&ex)[2][2][3], const R (&ey)
   R P00[2] = {}, P11[2] = {}, P22[2] = {};
   R P01[2][2] = {}, P02[2][2] = {}, P12[2][2] = {};
   bool ok = true;
-  const R wk = R(0.125 / kGA2) * kap;
-  const R wb = R(0.125 * kGA2) * bet;
+  const R wk = scale_by<R>(0.125 / kGA2, kap);
+  const R wb = scale_by<R>(0.125 * kGA2, bet);
 #pragma unroll
   for (int q3 = 0; q3 < 2; ++q3)
 #pragma unroll
