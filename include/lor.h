@@ -106,7 +106,7 @@ typedef struct lor_sched {
   int32_t nloc;                  /* local dofs per element */
   int32_t nent;                  /* local stencil entries per element */
   int32_t ncolors;
-  int32_t max_row_nnz;
+  int32_t max_row_nnz;           /* longest row (0: not counted, on H1 box lattices) */
   int32_t color_ptr[LOR_MAX_COLORS + 1];  /* colour c = order[color_ptr[c] .. color_ptr[c+1]) */
   int64_t nclass;
   int64_t tab_stride;            /* bytes between two element tables (nent rounded up to 16) */

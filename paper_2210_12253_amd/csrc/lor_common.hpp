@@ -122,6 +122,14 @@ inline int64_t march_segment(int64_t layers, int64_t tiles, int64_t slots, int64
   return seglen;
 }
 
+// Whether a mesh without an owner-computes schedule is assembled row by row:
+// up to `per_color` cells (all batch entries) per colour, and rows that fit 64 KB
+// of LDS (256 lanes, `lanes` per row; max_row_nnz 0: unknown).
+inline bool rows_pay(const lor_sched* s, int64_t cells, int64_t per_color, int lanes) {
+  const int row = (s->max_row_nnz > 0 ? s->max_row_nnz : LOR_MAX_ROW_NNZ) | 1;
+  return cells <= per_color * s->ncolors && 256 / lanes * row * 8 <= 64 * 1024;
+}
+
 template <typename T>
 inline T* dev_at(const lor_sched* s, size_t off) {
   return reinterpret_cast<T*>(static_cast<char*>(s->dev) + off);

@@ -450,8 +450,8 @@ int dispatch_owner(int p, const lor_sched* s, int batch, const double* x, const 
                    unsigned f, double thr, int32_t* diag, hipStream_t st);
 bool owner_fits(const lor_sched* s, int tsize);
 template <typename T>
-int dispatch_rows(int p, const lor_sched* s, int batch, const int32_t* ed, const double* x, const void* k, double beta,
-                  const int32_t* rp, void* v, unsigned f, double thr, int32_t* diag, hipStream_t st);
+int dispatch_h1_rows(int p, const lor_sched* s, int batch, const int32_t* verts, const int32_t* map, const double* x, const void* k,
+                     double beta, const int32_t* rp, void* v, unsigned f, double thr, int32_t* diag, hipStream_t st);
 
 // Shared argument checks of the value calls.
 int check_sched(const lor_sched* s, int space, int p, int64_t nel, int64_t nrows) {
@@ -469,8 +469,6 @@ int check_sched(const lor_sched* s, int space, int p, int64_t nel, int64_t nrows
 }  // namespace lor
 
 using namespace lor;
-
-static constexpr int64_t kRowCellsPerColor = 32000;
 
 extern "C" int lor_assemble_h1(int p, int64_t nel, int64_t ndofs, int batch, const int32_t* elem_dofs,
                                const double* coords, const void* kappa, double beta, const int32_t* row_ptr,
@@ -506,13 +504,13 @@ extern "C" int lor_assemble_h1(int p, int64_t nel, int64_t ndofs, int batch, con
   // (triangle-split meshes of 12 colours, p = 1 to 4): equal at about 32,000
   // cells per colour.
   const bool rows = !owner && !(flags & LOR_COLORED) &&
-                    nel * p * p * p * static_cast<int64_t>(batch) <= kRowCellsPerColor * sched->ncolors;
+                    rows_pay(sched, nel * p * p * p * static_cast<int64_t>(batch), 32000, 4);
   if (rows)
     return dtype == LOR_F64
-               ? dispatch_rows<double>(p, sched, batch, elem_dofs, coords, kappa, beta, row_ptr, values, 0u,
-                                       det_ratio_thresh, diag, st)
-               : dispatch_rows<float>(p, sched, batch, elem_dofs, coords, kappa, beta, row_ptr, values, fb,
-                                      det_ratio_thresh, diag, st);
+               ? dispatch_h1_rows<double>(p, sched, batch, elem_dofs, nullptr, coords, kappa, beta, row_ptr, values,
+                                          0u, det_ratio_thresh, diag, st)
+               : dispatch_h1_rows<float>(p, sched, batch, elem_dofs, nullptr, coords, kappa, beta, row_ptr, values, fb,
+                                         det_ratio_thresh, diag, st);
   if (dtype == LOR_F64)
     return owner ? dispatch_owner<double>(p, sched, batch, coords, kappa, beta, values, 0u, det_ratio_thresh, diag, st)
                  : dispatch_h1<double, double>(p, sched, batch, elem_dofs, coords, kappa, beta, row_ptr, values, 0u,

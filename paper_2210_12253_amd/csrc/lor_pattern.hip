@@ -699,6 +699,22 @@ __global__ __launch_bounds__(256) void k_color_greedy(const int32_t* __restrict_
   }
 }
 
+// Longest row.
+__global__ void k_max_row(const int32_t* __restrict__ row_ptr, int64_t nrows, int32_t* __restrict__ out) {
+  int32_t m = 0;
+  for (int64_t r = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; r < nrows;
+       r += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+    const int32_t n = row_ptr[r + 1] - row_ptr[r];
+    m = n > m ? n : m;
+  }
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int32_t t = __shfl_xor(m, d);
+    m = t > m ? t : m;
+  }
+  if ((threadIdx.x & 63) == 0) atomicMax(out, m);
+}
+
 // Every dof's incident elements must carry pairwise different colours.
 __global__ void k_check_colors(const int32_t* __restrict__ inc_ptr, const int32_t* __restrict__ inc_list,
                                int nloc, int64_t nrows, const int32_t* __restrict__ color,
@@ -1810,15 +1826,18 @@ static int general_schedule(lor_sched* s, const RefElem& ref, int is_signed, con
   {
     ArenaScope scope(a);
     LOR_TAKE(reps, a, int32_t, ref.reps.size());
-    LOR_TAKE(ncol, a, int32_t, 2);  // elements left uncoloured, highest colour
+    LOR_TAKE(ncol, a, int32_t, 3);  // elements left uncoloured, highest colour, longest row
     if ((rc = upload(ref.reps, reps, st))) return rc;
     if (nel > 0) {
       k_fill_i32<<<ceil_div(nel, 256), 256, 0, st>>>(d_color, nel, -1);
       LOR_LAUNCHED("k_fill_i32");
     }
-    k_fill_i32<<<1, 64, 0, st>>>(ncol, 2, 0);
+    k_fill_i32<<<1, 64, 0, st>>>(ncol, 3, 0);
     LOR_LAUNCHED("k_fill_i32");
-    int32_t left[2] = {0, 0}, before = static_cast<int32_t>(nel);
+    k_max_row<<<static_cast<unsigned>(std::min<int64_t>(ceil_div(nrows, 256), 1024)), 256, 0, st>>>(row_ptr, nrows,
+                                                                                                    ncol + 2);
+    LOR_LAUNCHED("k_max_row");
+    int32_t left[3] = {0, 0, 0}, before = static_cast<int32_t>(nel);
     while (before > 0) {
       k_color_greedy<<<ceil_div(nel * kColLanes, 256), 256, 0, st>>>(
           map, nloc, is_signed, reps, static_cast<int>(ref.reps.size()), d_inc_ptr, d_inc_list, nel, d_color,
@@ -1835,6 +1854,7 @@ static int general_schedule(lor_sched* s, const RefElem& ref, int is_signed, con
       }
     }
     ncolors = nel > 0 ? left[1] + 1 : 0;
+    s->max_row_nnz = left[2];
   }
   k_check_colors<<<ceil_div(nrows, 256), 256, 0, st>>>(d_inc_ptr, d_inc_list, nloc, nrows, d_color, d_err);
   LOR_LAUNCHED("k_check_colors");
@@ -2048,7 +2068,7 @@ extern "C" int lor_pattern(int space, int p, int64_t nel, int64_t nrows, const i
 
   // ------------------------------------------------------------------ phase 2
   if ((rc = a.alloc(box_ws + incidence_ws_bytes(nrows) + order_ws_bytes(nel) + ovf_ws_bytes(nrows) +
-                    arena_bytes<int32_t>(std::max<size_t>(ref.reps.size(), kBoxKeys)) + arena_bytes<int32_t>(2))))
+                    arena_bytes<int32_t>(std::max<size_t>(ref.reps.size(), kBoxKeys)) + arena_bytes<int32_t>(3))))
     return rc;
   LOR_TAKE(d_err, a, int32_t, 1);
   LOR_HIP(hipMemsetAsync(d_err, 0, sizeof(int32_t), st));

@@ -52,3 +52,34 @@ def test_h1_rows(kind, p):
                             det_ratio_thresh=1.02, diag=diag, kernel=kernel)
         counts.append(diag.cpu().tolist())
     assert counts[0] == counts[1]
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("space", ["nd", "rt"])
+@pytest.mark.parametrize("kind", ["prism5", "tri", "rotated"])
+def test_vector_rows(kind, space, p):
+    m, kap = _mesh(kind, p)
+    make = meshgen.edge_map_from_vertices if space == "nd" else meshgen.face_map_from_vertices
+    dm, n = make(m["elem_dofs"], p)
+    dm, _ = meshgen.flip_edge_signs(dm, n, seed=7)
+    ed, x, dmap = (torch.from_numpy(a).to(DEV) for a in (m["elem_dofs"], m["coords"], dm))
+    pat = lor.lor_pattern(lor.LOR_ND if space == "nd" else lor.LOR_RT, p, dmap, n)
+    assert not pat.owner
+    assert pat.sched.max_row_nnz == int((pat.row_ptr[1:] - pat.row_ptr[:-1]).max())
+    ref = orc.nd_matrix if space == "nd" else orc.rt_matrix
+    call = lor.lor_assemble_nd if space == "nd" else lor.lor_assemble_rt
+    rp, ci, v = ref(m["coords"], m["elem_dofs"], dm, p, kap, 0.7, n)
+    v64 = call(pat, ed, dmap, x, kap, 0.7, m["ndofs"])
+    assert row_rel_err(rp, ci, v64.cpu(), ci, v) <= 1e-12
+    v32 = call(pat, ed, dmap, x, kap.float(), 0.7, m["ndofs"], dtype=torch.float32)
+    assert row_rel_err(rp, ci, v32.cpu(), ci, v) <= 1e-6
+    check_whole_matrix(pat, v64, v32)
+    vb = call(pat, ed, dmap, x, torch.stack([kap, 0.5 * kap]), 0.7, m["ndofs"])
+    assert torch.equal(vb[0], v64)
+    counts = []
+    for kernel in ("auto", "colored"):
+        diag = torch.zeros(2, dtype=torch.int32, device=DEV)
+        call(pat, ed, dmap, x, kap.float(), 0.7, m["ndofs"], dtype=torch.float32, fp64_fallback=True,
+             det_ratio_thresh=1.02, diag=diag, kernel=kernel)
+        counts.append(diag.cpu().tolist())
+    assert counts[0] == counts[1]
