@@ -4,9 +4,7 @@
 //
 // A workgroup walks a chunk of macro elements of one colour, E at a time:
 //   phase 0  gather vertex coordinates, the row pointers and orientation
-//            signs of the element edges and the element rank table into LDS
-//            (in FP64 from registers filled while the previous group was
-//            computed);
+//            signs of the element edges and the element rank table into LDS;
 //   phase 1  one lane per subelement integrates its 12x12 matrix (78 unique
 //            entries) into LDS;
 //   phase 2  one lane per local stencil entry (edge l, edge l') sums the
@@ -36,15 +34,27 @@ struct NDCfg {
   static constexpr int NLOCE = 3 * P * Q * Q;   // edges per element
   static constexpr int NENT = 99 * P * P * P + 42 * P * P + 3 * P;  // local stencil entries
   static constexpr int NENTP = (NENT + 15) / 16 * 16;
-  static constexpr int THREADS = 256;
-  static constexpr int PER_EL = NSUB * 78 * static_cast<int>(sizeof(R)) + NENTP + NLOCV * 24 + NLOCE * 5;
-  // The kernel is latency bound (few elements per colour, short phases
-  // between barriers), so small groups and several resident workgroups per
-  // CU beat one large group per CU.  FP64 keeps 256 VGPRs per lane (two
-  // workgroups per CU) because the subelement integration spills below
-  // that; FP32 runs four workgroups per CU.
   static constexpr bool F64 = sizeof(R) == 8;
-  static constexpr int BUDGET = F64 ? 50 * 1024 : 30 * 1024;  // LDS for the per-element buffers
+  // The kernel is latency bound (a few elements per colour and CU, short phases
+  // between barriers).  Small elements: small groups and several resident
+  // workgroups per CU, of which one computes while another loads.  Large ones
+  // (p >= 4, one per workgroup): the lanes that the registers allow, for the entry
+  // sums are most of the time.  Triangle-split meshes, FP64, us:
+  //   lanes            128    256    512
+  //   p = 1, 138,000   256    252          (elements)
+  //   p = 2,  31,000   279    330
+  //   p = 3,   7,200   219    258
+  //   p = 4,   3,500   274    285    235
+  //   p = 5,   1,500   484    285    217
+  // FP32 (four waves per SIMD) 202 at 256 lanes and 204 at 128 for p = 2, 179 and 166
+  // for p = 3; 207 at 256 and 203 at 512 for p = 4, 264 and 211 for p = 5.
+  static constexpr int THREADS = P >= 4 ? 512 : P == 3 || (P == 2 && F64) ? 128 : 256;
+  static constexpr int PER_EL = NSUB * 78 * static_cast<int>(sizeof(R)) + NENTP + NLOCV * 24 + NLOCE * 5;
+  // FP64 keeps 256 VGPRs per lane (two waves per SIMD) because the subelement
+  // integration spills below that; FP32 runs four waves per SIMD.
+  static constexpr int WPS = F64 ? 2 : 4;
+  // LDS for the per-element buffers
+  static constexpr int BUDGET = 1024 * (F64 ? (P == 2 ? 24 : P == 3 ? 36 : 50) : (P == 3 ? 16 : 30));
   static constexpr int E0 = THREADS / NSUB < 64 ? THREADS / NSUB : 64;
   static constexpr int E1 = BUDGET / PER_EL;
   static constexpr int E = (E0 < E1 ? E0 : E1) > 0 ? (E0 < E1 ? E0 : E1) : 1;
@@ -53,16 +63,16 @@ struct NDCfg {
   static constexpr int NVS = (E * NLOCV + THREADS - 1) / THREADS;  // staged vertices per lane
   static constexpr int NES = (E * NLOCE + THREADS - 1) / THREADS;  // staged edges per lane
   static constexpr int NTS = (E * TWE + THREADS - 1) / THREADS;    // staged table words per lane
-  static constexpr int MAXCHUNK = 256;
+  static constexpr int MAXCHUNK = THREADS;
   static constexpr int LDS = E * PER_EL + 2 * MAXCHUNK * 4 + 256;
-  static constexpr int WPC0 = F64 ? 2 : 4;
+  static constexpr int WPC0 = WPS * 256 / THREADS > 0 ? WPS * 256 / THREADS : 1;
   static constexpr int WPC1 = 160 * 1024 / LDS;
   static constexpr int WPC = (WPC0 < WPC1 ? WPC0 : WPC1) > 0 ? (WPC0 < WPC1 ? WPC0 : WPC1) : 1;  // workgroups per CU
   static_assert(E * NSUB <= THREADS, "one subelement per lane");
 };
 
 template <int P, typename T, typename R>
-__global__ __launch_bounds__(256, (NDCfg<P, R>::WPC)) void k_nd_assemble(
+__global__ __launch_bounds__((NDCfg<P, R>::THREADS), (NDCfg<P, R>::WPS)) void k_nd_assemble(
     const int32_t* __restrict__ order, const int32_t* __restrict__ order_class, int32_t ncol, int32_t chunk,
     const int32_t* __restrict__ elem_dofs,
     const int32_t* __restrict__ elem_edges, const double* __restrict__ coords, const T* __restrict__ kappa, T beta,
@@ -93,81 +103,11 @@ __global__ __launch_bounds__(256, (NDCfg<P, R>::WPC)) void k_nd_assemble(
   }
   __syncthreads();
 
-  // FP64 staging is software-pipelined: the element-map words of group g + 2
-  // and the coordinates, row pointers, table words and coefficients of group
-  // g + 1 are loaded into registers while group g is computed.  FP32 runs four
-  // workgroups per CU at 128 VGPRs, where those registers spill; it gathers
-  // each group straight into LDS instead (measured: pipelining takes the
-  // p = 3 FP64 launch from 0.346 to 0.329 ms and the FP32 one from 0.202 to
-  // 0.221 ms).
+  // Each group is gathered straight into LDS: a launch has about one group per
+  // resident workgroup, so registers filled one group ahead only cost occupancy
+  // (FP64 with and without them: p = 1 252 and 229 us, p = 3 225 and 219).
   constexpr int NVS = C::NVS, NES = C::NES, NTS = C::NTS;
-  constexpr bool PIPE = C::F64;
   auto gsize = [&](int g) { return nce - g * E < E ? nce - g * E : E; };
-  auto load_ids = [&](int g, int32_t (&vid)[NVS], int32_t (&eid)[NES]) {
-    const int t = threadIdx.x;
-#pragma unroll
-    for (int j = 0; j < NVS; ++j) {
-      const int i = t + j * TH;
-      vid[j] = 0;
-      if (g < ngr && i < gsize(g) * NLOCV) {
-        const int el = i / NLOCV;
-        vid[j] = elem_dofs[static_cast<int64_t>(sOrd[g * E + el]) * NLOCV + (i - el * NLOCV)];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < NES; ++j) {
-      const int i = t + j * TH;
-      eid[j] = 0;
-      if (g < ngr && i < gsize(g) * NLOCE) {
-        const int el = i / NLOCE;
-        eid[j] = elem_edges[static_cast<int64_t>(sOrd[g * E + el]) * NLOCE + (i - el * NLOCE)];
-      }
-    }
-  };
-  auto load_data = [&](int g, const int32_t (&vid)[NVS], const int32_t (&eid)[NES], double (&xq)[NVS][3],
-                       int32_t (&rq)[NES], uint32_t (&tq)[NTS], T& kq) {
-    const int t = threadIdx.x;
-    if (g >= ngr) return;
-    const int n = gsize(g);
-#pragma unroll
-    for (int j = 0; j < NVS; ++j) {
-      if (t + j * TH < n * NLOCV) {
-        const int64_t v3 = 3 * static_cast<int64_t>(vid[j]);
-        xq[j][0] = coords[v3 + 0];
-        xq[j][1] = coords[v3 + 1];
-        xq[j][2] = coords[v3 + 2];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < NES; ++j) {
-      if (t + j * TH < n * NLOCE) rq[j] = row_ptr[eid[j] < 0 ? -1 - eid[j] : eid[j]];
-    }
-#pragma unroll
-    for (int j = 0; j < NTS; ++j) {
-      const int i = t + j * TH;
-      if (i < n * TWE) {
-        const int el = i / TWE;
-        tq[j] = reinterpret_cast<const uint32_t*>(tables + sCls[g * E + el] * tab_stride)[i - el * TWE];
-      }
-    }
-    if (t < n * NSUB) {
-      const int el = t / NSUB;
-      kq = kappa[static_cast<int64_t>(sOrd[g * E + el]) * NSUB + (t - el * NSUB)];
-    }
-  };
-  int32_t vid_n[NVS], eid_n[NES], eq[NES];
-  double xq[NVS][3] = {};
-  int32_t rq[NES] = {};
-  uint32_t tq[NTS] = {};
-  T kq = T(0);
-  if constexpr (PIPE) {
-    int32_t v0[NVS], e0[NES];
-    load_ids(0, v0, e0);
-    load_data(0, v0, e0, xq, rq, tq, kq);
-#pragma unroll
-    for (int j = 0; j < NES; ++j) eq[j] = e0[j];
-    load_ids(1, vid_n, eid_n);
-  }
 
   for (int g = 0; g < ngr; ++g) {
     int tid = threadIdx.x;
@@ -177,99 +117,69 @@ __global__ __launch_bounds__(256, (NDCfg<P, R>::WPC)) void k_nd_assemble(
     lds_barrier();  // the previous group is done with every LDS buffer
     // phase 0: stage the group in LDS
     T kcur = T(0);
-    if constexpr (PIPE) {
+    // every load of a phase before the first use: the map words, then the
+    // coordinates, row pointers, table words and the lane's coefficient
+    // (indices past the group clamped, their values not written)
+    int32_t vid[NVS], eid[NES];
 #pragma unroll
-      for (int j = 0; j < NVS; ++j) {
-        const int i = tid + j * TH;
-        if (i < ne * NLOCV) {
-          sX[3 * i + 0] = xq[j][0];
-          sX[3 * i + 1] = xq[j][1];
-          sX[3 * i + 2] = xq[j][2];
-        }
+    for (int j = 0; j < NVS; ++j) {
+      const int i = tid + j * TH;
+      const int i2 = i < ne * NLOCV ? i : 0;
+      const int el = i2 / NLOCV;
+      vid[j] = elem_dofs[static_cast<int64_t>(sOrd[g * E + el]) * NLOCV + (i2 - el * NLOCV)];
+    }
+#pragma unroll
+    for (int j = 0; j < NES; ++j) {
+      const int i = tid + j * TH;
+      const int i2 = i < ne * NLOCE ? i : 0;
+      const int el = i2 / NLOCE;
+      eid[j] = elem_edges[static_cast<int64_t>(sOrd[g * E + el]) * NLOCE + (i2 - el * NLOCE)];
+    }
+    uint32_t tw[NTS];
+#pragma unroll
+    for (int j = 0; j < NTS; ++j) {
+      const int i = tid + j * TH;
+      const int i2 = i < ne * TWE ? i : 0;
+      const int el = i2 / TWE;
+      tw[j] = reinterpret_cast<const uint32_t*>(tables + sCls[g * E + el] * tab_stride)[i2 - el * TWE];
+    }
+    {
+      const int t2 = tid < ne * NSUB ? tid : 0;
+      const int el = t2 / NSUB;
+      kcur = kappa[static_cast<int64_t>(sOrd[g * E + el]) * NSUB + (t2 - el * NSUB)];
+    }
+    double xv[NVS][3];
+    int32_t rv[NES];
+#pragma unroll
+    for (int j = 0; j < NVS; ++j) {
+      const int64_t v3 = 3 * static_cast<int64_t>(vid[j]);
+      xv[j][0] = coords[v3 + 0];
+      xv[j][1] = coords[v3 + 1];
+      xv[j][2] = coords[v3 + 2];
+    }
+#pragma unroll
+    for (int j = 0; j < NES; ++j) rv[j] = row_ptr[eid[j] < 0 ? -1 - eid[j] : eid[j]];
+#pragma unroll
+    for (int j = 0; j < NVS; ++j) {
+      const int i = tid + j * TH;
+      if (i < ne * NLOCV) {
+        sX[3 * i + 0] = xv[j][0];
+        sX[3 * i + 1] = xv[j][1];
+        sX[3 * i + 2] = xv[j][2];
       }
+    }
 #pragma unroll
-      for (int j = 0; j < NES; ++j) {
-        const int i = tid + j * TH;
-        if (i < ne * NLOCE) {
-          sRp[i] = rq[j];
-          sSg[i] = eq[j] < 0 ? 1 : 0;
-        }
+    for (int j = 0; j < NES; ++j) {
+      const int i = tid + j * TH;
+      if (i < ne * NLOCE) {
+        sRp[i] = rv[j];
+        sSg[i] = eid[j] < 0 ? 1 : 0;
       }
+    }
 #pragma unroll
-      for (int j = 0; j < NTS; ++j) {
-        const int i = tid + j * TH;
-        if (i < ne * TWE) sTabW[i] = tq[j];
-      }
-      kcur = kq;
-      load_data(g + 1, vid_n, eid_n, xq, rq, tq, kq);
-#pragma unroll
-      for (int j = 0; j < NES; ++j) eq[j] = eid_n[j];
-      load_ids(g + 2, vid_n, eid_n);
-    } else {
-      // every load of a phase before the first use: the map words, then the
-      // coordinates, row pointers, table words and the lane's coefficient
-      // (indices past the group clamped, their values not written)
-      int32_t vid[NVS], eid[NES];
-#pragma unroll
-      for (int j = 0; j < NVS; ++j) {
-        const int i = tid + j * TH;
-        const int i2 = i < ne * NLOCV ? i : 0;
-        const int el = i2 / NLOCV;
-        vid[j] = elem_dofs[static_cast<int64_t>(sOrd[g * E + el]) * NLOCV + (i2 - el * NLOCV)];
-      }
-#pragma unroll
-      for (int j = 0; j < NES; ++j) {
-        const int i = tid + j * TH;
-        const int i2 = i < ne * NLOCE ? i : 0;
-        const int el = i2 / NLOCE;
-        eid[j] = elem_edges[static_cast<int64_t>(sOrd[g * E + el]) * NLOCE + (i2 - el * NLOCE)];
-      }
-      uint32_t tw[NTS];
-#pragma unroll
-      for (int j = 0; j < NTS; ++j) {
-        const int i = tid + j * TH;
-        const int i2 = i < ne * TWE ? i : 0;
-        const int el = i2 / TWE;
-        tw[j] = reinterpret_cast<const uint32_t*>(tables + sCls[g * E + el] * tab_stride)[i2 - el * TWE];
-      }
-      {
-        const int t2 = tid < ne * NSUB ? tid : 0;
-        const int el = t2 / NSUB;
-        kcur = kappa[static_cast<int64_t>(sOrd[g * E + el]) * NSUB + (t2 - el * NSUB)];
-      }
-      double xv[NVS][3];
-      int32_t rv[NES];
-#pragma unroll
-      for (int j = 0; j < NVS; ++j) {
-        const int64_t v3 = 3 * static_cast<int64_t>(vid[j]);
-        xv[j][0] = coords[v3 + 0];
-        xv[j][1] = coords[v3 + 1];
-        xv[j][2] = coords[v3 + 2];
-      }
-#pragma unroll
-      for (int j = 0; j < NES; ++j) rv[j] = row_ptr[eid[j] < 0 ? -1 - eid[j] : eid[j]];
-#pragma unroll
-      for (int j = 0; j < NVS; ++j) {
-        const int i = tid + j * TH;
-        if (i < ne * NLOCV) {
-          sX[3 * i + 0] = xv[j][0];
-          sX[3 * i + 1] = xv[j][1];
-          sX[3 * i + 2] = xv[j][2];
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < NES; ++j) {
-        const int i = tid + j * TH;
-        if (i < ne * NLOCE) {
-          sRp[i] = rv[j];
-          sSg[i] = eid[j] < 0 ? 1 : 0;
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < NTS; ++j) {
-        const int i = tid + j * TH;
-        if (i < ne * TWE) sTabW[i] = tw[j];
-      }
+    for (int j = 0; j < NTS; ++j) {
+      const int i = tid + j * TH;
+      if (i < ne * TWE) sTabW[i] = tw[j];
     }
     lds_barrier();
 
@@ -478,12 +388,12 @@ extern "C" int lor_assemble_nd(int p, int64_t nel, int64_t ndofs_h1, int64_t ned
   // which the coloured kernel does not take)
   const bool owner = sched->owner && !(flags & LOR_COLORED);
   const unsigned fb = flags & LOR_FP64_FALLBACK;
-  // Elsewhere (p <= 5): row by row on small meshes, in colours on large ones:
-  // 15 us + 1.85 us per 1,000 cells against about 13 us per colour + 0.9 us per
-  // 1,000 cells (triangle-split meshes of 9 to 12 colours): equal at about
-  // 10,000 cells per colour.
+  // Elsewhere (p <= 5): row by row on small meshes, in colours on large ones.
+  // Triangle-split meshes of 9 colours, rows and colours: 5,800 cells per colour
+  // 102 and 137 us (p = 3), 112 and 161 (p = 1); 8,800 149 and 141 us (p = 3);
+  // 8,000 137 and 251 (p = 5).  The line is where p = 3 crosses.
   const bool rows = !owner && !(flags & LOR_COLORED) && p <= 5 &&
-                    rows_pay(sched, nel * p * p * p * static_cast<int64_t>(batch), 10000, 4);
+                    rows_pay(sched, nel * p * p * p * static_cast<int64_t>(batch), 8500, 4);
   if (rows)
     return dtype == LOR_F64 ? dispatch_nd_rows<double>(p, sched, batch, elem_dofs, elem_edges, coords, kappa, beta, row_ptr, values, 0u,
                                          det_ratio_thresh, diag, st)
