@@ -37,12 +37,18 @@ struct H1Cfg {
   static constexpr int NENT = T1 * T1 * T1;        // local stencil entries per element
   static constexpr int NENTP = (NENT + 15) / 16 * 16;  // table stride in bytes
   // Elements per group: the workgroup's lanes cover the subelements and every
-  // lane owns at most two local rows.  128 lanes where they do (p <= 5): with
-  // 256 and twice the elements, p = 3 to 5 held one workgroup per CU (88 to 98 KB
-  // of LDS in FP64), whose phases nothing overlapped; p = 5, 7,200 elements:
-  // 295 -> 214 us.
-  static constexpr int E = P == 1 ? 32 : P == 2 ? 8 : P == 3 ? 4 : P == 4 ? 2 : 1;
-  static constexpr int THREADS = P == 6 ? 256 : 128;
+  // lane owns at most two local rows.  The fewest waves that do, so that several
+  // workgroups are on a CU and one computes while the others load and store (with
+  // 256 lanes and four times the elements, p = 3 to 5 held one workgroup per CU).
+  // Triangle-split meshes, FP64, us:
+  //   lanes            64     128    256
+  //   p = 1, 2 million 1648   1707           (elements)
+  //   p = 2, 311,000   954    972
+  //   p = 3, 90,000    652    713
+  //   p = 4, 7,200     168    208
+  //   p = 5, 7,200            213    295
+  static constexpr int E = P == 1 ? 8 : P == 2 ? 4 : 1;
+  static constexpr int THREADS = P == 6 ? 256 : P == 5 ? 128 : 64;
   static constexpr int RV = (E * NLOC + THREADS - 1) / THREADS;         // vertex slots per lane
   static constexpr int TW = E * NENTP / 4;                             // table words per group
   static constexpr int RW = (TW + THREADS - 1) / THREADS;              // table words per lane
@@ -500,11 +506,14 @@ extern "C" int lor_assemble_h1(int p, int64_t nel, int64_t ndofs, int batch, con
   const unsigned fb = flags & LOR_FP64_FALLBACK;
   // Elsewhere: row by row on small meshes, in colours on large ones.  One launch
   // that integrates every cell eight times costs 10 us + 0.43 us per 1,000
-  // cells, a launch per colour about 12 us each + 0.1 us per 1,000 cells in all
-  // (triangle-split meshes of 12 colours, p = 1 to 4): equal at about 32,000
-  // cells per colour.
+  // cells, a launch per colour 9 to 12 us each and 0.1 to 0.3 us per 1,000 cells,
+  // more where the elements are small.  Triangle-split meshes of 12 colours, rows
+  // and colours, us: p = 1 22,500 cells per colour 136 and 253; p = 2 33,700 207
+  // and 210; p = 3 19,600 126 and 121; p = 4 22,500 134 and 146, 28,500 165 and 155;
+  // p = 5 27,600 158 and 160; p = 6 27,200 152 and 158, 35,000 190 and 165.
+  const int64_t per_color = p <= 2 ? 32000 : p == 3 ? 19000 : 26000;
   const bool rows = !owner && !(flags & LOR_COLORED) &&
-                    rows_pay(sched, nel * p * p * p * static_cast<int64_t>(batch), 32000, 4);
+                    rows_pay(sched, nel * p * p * p * static_cast<int64_t>(batch), per_color, 4);
   if (rows)
     return dtype == LOR_F64
                ? dispatch_h1_rows<double>(p, sched, batch, elem_dofs, nullptr, coords, kappa, beta, row_ptr, values,

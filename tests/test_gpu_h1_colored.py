@@ -29,7 +29,7 @@ def test_many_groups_match_the_oracle(p, n, layers):
 
 
 def test_more_elements_per_workgroup_than_lanes():
-    """p = 1 on a box large enough for 8 groups of 32 elements per workgroup."""
+    """p = 1 on a box large enough for more than 64 elements per workgroup of 64 lanes."""
     m = meshgen.box_mesh(160, 160, 128, 1, 0.1)
     kap = meshgen.kappa_field(m["nel"], 1, 1.0, seed=1)
     ed, x = torch.from_numpy(m["elem_dofs"]).to(DEV), torch.from_numpy(m["coords"]).to(DEV)
