@@ -34,7 +34,9 @@ struct RTCfg {
   // element, 6 for each of its 6P^2 boundary faces
   static constexpr int NENT = 33 * P * P * P + 3 * P * P;
   static constexpr int NENTP = (NENT + 15) / 16 * 16;
-  static constexpr int THREADS = 256;
+  // (p = 6, one element per workgroup: 617 us at 256 lanes and 523 at 512 on 10,000
+  // elements of a triangle-split mesh; p = 4 233 and 274, p = 3 186 and 250)
+  static constexpr int THREADS = P >= 6 ? 512 : 256;
   static constexpr int PER_EL = NSUB * 21 * static_cast<int>(sizeof(R)) + NENTP + NLOCV * 24 + NLOCF * 5;
   // latency bound like the H(curl) kernel: small groups (2 elements at
   // p = 3) and up to 4 resident workgroups per CU, as LDS allows; the RT
@@ -46,16 +48,16 @@ struct RTCfg {
   static constexpr int E = (E0 < E1 ? E0 : E1) > 0 ? (E0 < E1 ? E0 : E1) : 1;
   static constexpr int TWE = NENTP / 4;
   static constexpr int CH = 8;  // phase-2 entries per lane handled together
-  static constexpr int MAXCHUNK = 256;
+  static constexpr int MAXCHUNK = THREADS;
   static constexpr int LDS = E * PER_EL + 2 * MAXCHUNK * 4 + 256;
-  static constexpr int WPC0 = 4;
+  static constexpr int WPC0 = 4 * 256 / THREADS;
   static constexpr int WPC1 = 160 * 1024 / LDS;
   static constexpr int WPC = (WPC0 < WPC1 ? WPC0 : WPC1) > 0 ? (WPC0 < WPC1 ? WPC0 : WPC1) : 1;
   static_assert(E * NSUB <= THREADS, "one subelement per lane");
 };
 
 template <int P, typename T, typename R>
-__global__ __launch_bounds__(256, (RTCfg<P, R>::WPC)) void k_rt_assemble(
+__global__ __launch_bounds__((RTCfg<P, R>::THREADS), (RTCfg<P, R>::WPC * RTCfg<P, R>::THREADS / 256)) void k_rt_assemble(
     const int32_t* __restrict__ order, const int32_t* __restrict__ order_class, int32_t ncol, int32_t chunk,
     const int32_t* __restrict__ elem_dofs, const int32_t* __restrict__ elem_faces, const double* __restrict__ coords,
     const T* __restrict__ kappa, T beta, const int32_t* __restrict__ row_ptr, const uint8_t* __restrict__ tables,

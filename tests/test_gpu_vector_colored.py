@@ -1,7 +1,7 @@
-"""The coloured H(curl) kernel where a workgroup walks several groups of elements
-(more elements per colour than the resident workgroups take, with a remainder in
-the last group and the last workgroup), against the owner-computes kernel on the
-same box, and batches against single calls."""
+"""The coloured H(curl) and H(div) kernels where a workgroup walks several groups
+of elements (more elements per colour than the resident workgroups take, with a
+remainder in the last group and the last workgroup), against the owner-computes
+kernels on the same box, and batches against single calls."""
 import pytest
 import torch
 
@@ -32,3 +32,22 @@ def test_groups(p, n):
     assert row_rel_err(rp, ci, c32.cpu(), ci, own.cpu().numpy()) <= 1e-6
     vb = lor.lor_assemble_nd(pat, ed, ee, x, torch.stack([kap, 0.5 * kap]), 0.7, m["ndofs"], kernel="colored")
     assert torch.equal(vb[0], col)
+
+
+def test_rt_groups():
+    """H(div) at p = 6, one element per workgroup of eight waves: about 600
+    elements per colour on 512 resident workgroups."""
+    n, p = (11, 11, 10), 6
+    m = meshgen.box_mesh(*n, p, 0.1)
+    kap = meshgen.kappa_field(m["nel"], p, 1.0, seed=1)
+    fm, nfaces = meshgen.face_map_box(*n, p)
+    fm, _ = meshgen.flip_edge_signs(fm, nfaces, seed=7)
+    ed, x, ff = (torch.from_numpy(a).to(DEV) for a in (m["elem_dofs"], m["coords"], fm))
+    pat = lor.lor_pattern(lor.LOR_RT, p, ff, nfaces)
+    assert pat.owner
+    rp, ci = pat.row_ptr.cpu().numpy(), pat.col_idx.cpu().numpy()
+    own = lor.lor_assemble_rt(pat, ed, ff, x, kap, 0.7, m["ndofs"])
+    col = lor.lor_assemble_rt(pat, ed, ff, x, kap, 0.7, m["ndofs"], kernel="colored")
+    assert row_rel_err(rp, ci, col.cpu(), ci, own.cpu().numpy()) <= 1e-12
+    c32 = lor.lor_assemble_rt(pat, ed, ff, x, kap.float(), 0.7, m["ndofs"], dtype=torch.float32, kernel="colored")
+    assert row_rel_err(rp, ci, c32.cpu(), ci, own.cpu().numpy()) <= 1e-6
