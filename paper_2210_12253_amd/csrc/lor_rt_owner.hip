@@ -21,6 +21,13 @@
 //   * every row type's finished rows of a line (X consecutive) are
 //     consecutive rows of the matrix: staged in LDS and stored as one span.
 //
+// What bounds it: one wave's step takes about 4 us, mostly the integration and the
+// latency between its phases, with two waves per SIMD (three spill: 67 us against
+// 50).  Barriers that wait for LDS only, lines addressed by one lane each instead
+// of by scalar arithmetic in every step (125 spilled scalars), columns by one
+// fused multiply-add per value and axis: p = 3, 24^3 56.7 -> 51.7 us, FP32 50.5 ->
+// 44.1, 7 x 7 x 8 14.7 -> 12.1.
+//
 // Two distinct faces share at most one cell, so every off-diagonal entry has
 // one term and the matrix is bitwise symmetric; a diagonal entry takes its
 // two cells in a fixed order.  All sums are FP64, in the FP32 form too.  The
@@ -40,26 +47,25 @@ constexpr int kRtLineIters = (kRtLine + 63) / 64;
 
 // Entries before face X of a row of faces 0 .. M (the faces at 0 and M have 6
 // entries, the others 11), X in [0, M + 1].
-__host__ __device__ __forceinline__ int64_t rt_prefix(int64_t X, int64_t M) {
+__host__ __device__ __forceinline__ int rt_prefix(int X, int M) {
   if (X <= 0) return 0;
   if (X <= M) return 6 + 11 * (X - 1);
   return 12 + 11 * (M - 1);
 }
-__host__ __device__ __forceinline__ int rt_len(int64_t X, int64_t M) { return (X == 0 || X == M) ? 6 : 11; }
+__host__ __device__ __forceinline__ int rt_len(int X, int M) { return (X == 0 || X == M) ? 6 : 11; }
 
 // Row starts of the face-lattice pattern (x-face rows, then y-face rows, then
-// z-face rows, each in face-id order).
+// z-face rows, each in face-id order); an int holds them, for a pattern has fewer
+// than 2^31 entries.
 struct RtLattice {
-  int64_t MX, MY, MZ;
-  __host__ __device__ int64_t nnz_x() const { return MY * MZ * rt_prefix(MX + 1, MX); }
-  __host__ __device__ int64_t nnz_y() const { return MZ * MX * rt_prefix(MY + 1, MY); }
-  __host__ __device__ int64_t row_x(int64_t X, int64_t Y, int64_t Z) const {
-    return (Y + MY * Z) * rt_prefix(MX + 1, MX) + rt_prefix(X, MX);
-  }
-  __host__ __device__ int64_t row_y(int64_t X, int64_t Y, int64_t Z) const {
+  int MX, MY, MZ;
+  __device__ int nnz_x() const { return MY * MZ * rt_prefix(MX + 1, MX); }
+  __device__ int nnz_y() const { return MZ * MX * rt_prefix(MY + 1, MY); }
+  __device__ int row_x(int X, int Y, int Z) const { return (Y + MY * Z) * rt_prefix(MX + 1, MX) + rt_prefix(X, MX); }
+  __device__ int row_y(int X, int Y, int Z) const {
     return nnz_x() + Z * MX * rt_prefix(MY + 1, MY) + MX * rt_prefix(Y, MY) + X * rt_len(Y, MY);
   }
-  __host__ __device__ int64_t row_z(int64_t X, int64_t Y, int64_t Z) const {
+  __device__ int row_z(int X, int Y, int Z) const {
     return nnz_x() + nnz_y() + MX * MY * rt_prefix(Z, MZ) + (X + MX * Y) * rt_len(Z, MZ);
   }
 };
@@ -108,7 +114,7 @@ __device__ __noinline__ bool rt_owner_fp64_fallback(const int32_t* __restrict__ 
 }
 
 template <int P, typename T, typename R>
-__global__ __launch_bounds__(64) void k_rt_owner(int nex, int ney, int nez, int ntx, int seglen,
+__global__ __launch_bounds__(64, 2) void k_rt_owner(int nex, int ney, int nez, int ntx, int seglen,
                                                 const int32_t* __restrict__ elem3d,
                                                 const int32_t* __restrict__ elem_dofs,
                                                 const int32_t* __restrict__ elem_faces,
@@ -280,51 +286,8 @@ __global__ __launch_bounds__(64) void k_rt_owner(int nex, int ney, int nez, int 
     corner_xyz(idn, hin);
     int32_t idn2[4];
     corner_ids(el2, Z + 2, 1, idn2);
-    __syncthreads();
+    lds_barrier();
 
-    // the three rows of this lane, each at the interior positions; the terms
-    // of a missing cell are absent (0)
-    double rx[11], ry[11], rz[11];
-#pragma unroll
-    for (int k = 0; k < 11; ++k) {
-      rx[k] = 0.0;
-      ry[k] = 0.0;
-      rz[k] = 0.0;
-    }
-#pragma unroll
-    for (int v = 0; v < 6; ++v) rz[rt_pos(2, 0, v)] = carry[v];
-    if (Z < MZ) {
-      // x-face at X: the cell X - 1 (lane x - 1, its x+ face) then the cell X
-      if (lx > 0 && X - 1 < MX && Y < MY) {
-        const R* cm = sCell + lane - 1;
-#pragma unroll
-        for (int v = 0; v < 6; ++v) rx[rt_pos(0, 0, v)] += static_cast<double>(cm[pair_index6(1, v) * 64]);
-      }
-      if (cell) {
-#pragma unroll
-        for (int v = 0; v < 6; ++v)
-          rx[rt_pos(0, 1, v)] += static_cast<double>(sCell[pair_index6(0, v) * 64 + lane]);
-      }
-      // y-face at Y: the cell Y - 1 (lane y - 1, its y+ face) then the cell Y
-      if (ly > 0 && X < MX && Y - 1 < MY) {
-        const R* cm = sCell + lane - 8;
-#pragma unroll
-        for (int v = 0; v < 6; ++v) ry[rt_pos(1, 0, v)] += static_cast<double>(cm[pair_index6(3, v) * 64]);
-      }
-      if (cell) {
-#pragma unroll
-        for (int v = 0; v < 6; ++v)
-          ry[rt_pos(1, 1, v)] += static_cast<double>(sCell[pair_index6(2, v) * 64 + lane]);
-        // z-face at Z: the carry (cell Z - 1), then this cell's z- face; its
-        // z+ face is the next carry
-#pragma unroll
-        for (int v = 0; v < 6; ++v) {
-          rz[rt_pos(2, 1, v)] += static_cast<double>(sCell[pair_index6(4, v) * 64 + lane]);
-          carry[v] = static_cast<double>(sCell[pair_index6(5, v) * 64 + lane]);
-        }
-      }
-    }
-    __syncthreads();
     // the next layer's cell: its lower corners are this cell's upper ones
 #pragma unroll
     for (int v = 0; v < 4; ++v)
@@ -340,35 +303,79 @@ __global__ __launch_bounds__(64) void k_rt_owner(int nex, int ney, int nez, int 
     kq = kn;
     elc = el1;
     el1 = el2;
-    if (Z < zs) continue;  // the layer below the segment: carry only
+    // the cell's z+ face is the next layer's carry
+    auto take_carry = [&] {
+#pragma unroll
+      for (int v = 0; v < 6; ++v) carry[v] = cell ? static_cast<double>(sCell[pair_index6(5, v) * 64 + lane]) : 0.0;
+    };
+    if (Z < zs) {  // the layer below the segment: carry only
+      take_carry();
+      lds_barrier();
+      continue;
+    }
 
-    // stage and store one row type at a time: line l of the tile holds the
-    // owned rows of that line in face-id order (X consecutive)
+    // sum, stage and store one row type at a time: line l of the tile holds the
+    // owned rows of that line in face-id order (X consecutive).  Lane 8 axis + l
+    // works out where line l starts in the matrix and how many entries it has
+    // (the matrix has fewer than 2^31)
+    int lstart = 0, lspan = 0;
+    {
+      const int axis = lane >> 3, l = lane & 7, Yl = y0 + l;
+      const bool in = l > 0 || tj == 0;
+      if (axis == 0) {
+        if (Z < MZ && Yl < MY && in) {
+          lstart = lat.row_x(xa, Yl, Z);
+          lspan = rt_prefix(xe + 1, MX) - rt_prefix(xa, MX);
+        }
+      } else if (axis == 1) {
+        if (Z < MZ && Yl <= MY && in && xce >= xa) {
+          lstart = lat.row_y(xa, Yl, Z);
+          lspan = (xce - xa + 1) * rt_len(Yl, MY);
+        }
+      } else if (axis == 2) {
+        if (Yl < MY && in && xce >= xa) {
+          lstart = lat.row_z(xa, Yl, Z);
+          lspan = (xce - xa + 1) * rt_len(Z, MZ);
+        }
+      }
+    }
+#pragma unroll
     for (int axis = 0; axis < 3; ++axis) {
-      // this lane's row of this type, its line and its first owned row
+      // this lane's row of this type and the entries of its line before it
       bool mine;
-      int len, before, first, last;
+      int before;
       if (axis == 0) {  // x-face (X, Y, Z): Y < MY, Z < MZ, X in [xa, xe]
         mine = Z < MZ && Y < MY && ly >= (tj > 0) && X >= xa && X <= xe;
-        len = rt_len(X, MX);
-        before = static_cast<int>(rt_prefix(X, MX) - rt_prefix(xa, MX));
-        first = xa;
-        last = xe;
+        before = rt_prefix(X, MX) - rt_prefix(xa, MX);
       } else if (axis == 1) {  // y-face (X, Y, Z): X a cell column, Y in [ya, ye2], Z < MZ
         mine = Z < MZ && X < MX && lx >= (ti > 0) && X <= xce && Y >= ya && Y <= ye2;
-        len = rt_len(Y, MY);
-        before = (X - xa) * len;
-        first = xa;
-        last = xce;
+        before = (X - xa) * rt_len(Y, MY);
       } else {  // z-face (X, Y, Z): a cell column, Z <= MZ
         mine = X < MX && Y < MY && lx >= (ti > 0) && ly >= (tj > 0) && X <= xce && Y <= yce;
-        len = rt_len(Z, MZ);
-        before = (X - xa) * len;
-        first = xa;
-        last = xce;
+        before = (X - xa) * rt_len(Z, MZ);
+      }
+      // the row at the interior positions, the cell before the face then the
+      // one after it (z: the carry is the one before); a missing cell's terms
+      // are absent (0)
+      double r[11];
+#pragma unroll
+      for (int k = 0; k < 11; ++k) r[k] = 0.0;
+      if (axis == 2) {
+#pragma unroll
+        for (int v = 0; v < 6; ++v) r[rt_pos(2, 0, v)] = carry[v];
+        take_carry();
+      } else if (Z < MZ && (axis == 0 ? lx > 0 && X - 1 < MX && Y < MY : ly > 0 && X < MX && Y - 1 < MY)) {
+        const R* cm = sCell + lane - (axis == 0 ? 1 : 8);
+#pragma unroll
+        for (int v = 0; v < 6; ++v)
+          r[rt_pos(axis, 0, v)] += static_cast<double>(cm[pair_index6(2 * axis + 1, v) * 64]);
+      }
+      if (cell) {
+#pragma unroll
+        for (int v = 0; v < 6; ++v)
+          r[rt_pos(axis, 1, v)] += static_cast<double>(sCell[pair_index6(2 * axis, v) * 64 + lane]);
       }
       if (mine) {
-        const double* r = axis == 0 ? rx : axis == 1 ? ry : rz;
         T* dst = sStg + kRtLine * ly + before;
         const int A = axis == 0 ? X : axis == 1 ? Y : Z;
         const int M = axis == 0 ? MX : axis == 1 ? MY : MZ;
@@ -383,41 +390,18 @@ __global__ __launch_bounds__(64) void k_rt_owner(int nex, int ney, int nez, int 
           for (int v = 0; v < 6; ++v) dst[v] = static_cast<T>(r[rt_pos(axis, 0, v)]);
         }
       }
-      __syncthreads();
-      // line l: the rows [first, last] of line y0 + l (the same for every lane)
+      lds_barrier();
 #pragma unroll
       for (int l = 0; l < kRtTile; ++l) {
-        const int Yl = y0 + l;
-        bool line;
-        int64_t ls = 0;
-        int span = 0;
-        if (axis == 0) {
-          line = Z < MZ && Yl < MY && (l > 0 || tj == 0);
-          if (line) {
-            ls = lat.row_x(first, Yl, Z);
-            span = static_cast<int>(rt_prefix(last + 1, MX) - rt_prefix(first, MX));
-          }
-        } else if (axis == 1) {
-          line = Z < MZ && Yl <= MY && (l > 0 || tj == 0) && last >= first;
-          if (line) {
-            ls = lat.row_y(first, Yl, Z);
-            span = (last - first + 1) * rt_len(Yl, MY);
-          }
-        } else {
-          line = Yl < MY && (l > 0 || tj == 0) && last >= first;
-          if (line) {
-            ls = lat.row_z(first, Yl, Z);
-            span = (last - first + 1) * rt_len(Z, MZ);
-          }
-        }
-        T* dst = values + ls;
+        const int span = __builtin_amdgcn_readlane(lspan, 8 * axis + l);
+        T* dst = values + __builtin_amdgcn_readlane(lstart, 8 * axis + l);
 #pragma unroll
         for (int it = 0; it < kRtLineIters; ++it) {
           const int t = lane + 64 * it;
           if (t < span) dst[t] = sStg[kRtLine * l + t];
         }
       }
-      __syncthreads();
+      lds_barrier();
     }
   }
 }
