@@ -3,14 +3,14 @@
 // L = sum_b <Gbar_b, A_b>,  A_b = sum_s kappa_{b,s} K^s + beta M^s  (K^s at kappa = 1).
 //   dL/dkappa_{b,s} = sum_{u,v} Gbar_b[pos(s,u,v)] K^s_uv,
 //   dL/dX = sum_s <sum_b kappa_{b,s} Gbar_b|s, dK^s/dX> + <sum_b Gbar_b|s, dM^s/dX>.
-// One lane per subelement recomputes the geometry and K^s (nothing is stored
-// by the forward pass), gathers the cotangent at the 64 CSR positions of its
-// 8x8 block for every batch entry, writes dL/dkappa, and runs the reverse of
-// the sum-factorised integration to get the adjoint of its 8 corner
-// coordinates.  The corners are summed per element vertex in LDS in a fixed
-// order (element E-vector), then per global vertex over its sorted
-// incidences (deterministic; coordinates are shared by the batch, so their
-// gradient is the sum over the batch).
+// One lane per subelement (or two, with half of its corner pairs each)
+// recomputes the geometry and K^s (nothing is stored by the forward pass),
+// gathers the cotangent at the 64 CSR positions of its 8x8 block for every batch
+// entry, writes dL/dkappa, and runs the reverse of the sum-factorised integration
+// to get the adjoint of its 8 corner coordinates.  The corners are summed per
+// element vertex in LDS in a fixed order (element E-vector), then per global
+// vertex over its sorted incidences (deterministic; coordinates are shared by the
+// batch, so their gradient is the sum over the batch).
 #include <mutex>
 
 #include "lor_common.hpp"
@@ -63,20 +63,42 @@ struct BwCfg {
   static constexpr int NENT = T1 * T1 * T1;
   static constexpr int NENTP = (NENT + 15) / 16 * 16;
   static constexpr int E = NSUB >= 64 ? 1 : 64 / NSUB;
-  static constexpr int THREADS = (E * NSUB + 63) / 64 * 64;
+  static constexpr int LANES = (E * NSUB + 63) / 64 * 64;  // one per subelement
   static constexpr int TWE = NENTP / 4;
 };
 
-// Waves per SIMD to reserve registers for: one.  A lane keeps 108
-// accumulators, the next batch entry's gathered cotangents and its 64 packed
-// pair indices in registers; at two waves per SIMD the FP32 form spills
-// (measured at p = 4, 16^3, batch 8: 0.192 ms at two waves with 57 spilled
-// registers, 0.143 ms at one).
-template <typename R>
-struct BwOcc {
-  static constexpr int WPE = 1;
-};
+// The unique pairs (u <= v) that lane h of the H of a subelement takes: all, or those
+// of 18 of 36 whose lower corner is 0, 3, 4 or 7 (or not); pair_slot: how many of
+// lane 1's come before (u, v).
+template <int H>
+__host__ __device__ constexpr bool pair_of(int h, int u) {
+  return H == 1 || (u == 0 || u == 3 || u == 4 || u == 7) == (h == 0);
+}
+__host__ __device__ constexpr int pair_slot(int u, int v) {
+  int n = 0;
+  for (int a = 0; a < u; ++a) n += pair_of<2>(1, a) ? 8 - a : 0;
+  return n + v - u;
+}
 
+// Lanes per subelement (H) and waves per SIMD to reserve registers for (WPS).  The
+// kernel waits more than it computes (FP64, p = 4, batch 8: VALU issue in 36% of
+// a wave's cycles), so waves are what it wants, but a lane keeps 108 accumulators
+// (K, and the adjoints of K and M, per corner pair) and the next batch entry's
+// gathered cotangents.  FP32: two lanes share a subelement, each with 18 of the 36
+// pairs until the batch is through, and a register budget of two or three waves.
+// In FP64 that spills 40 to 60 registers.  Batch 8, boxes, us with
+// one lane and one wave / two lanes and two waves / two lanes and three waves:
+//   FP64  p = 2, 20^3   90 / 125         p = 4, 16^3  191 / 231
+//   FP32  p = 2, 20^3   74 /  57 /  60   p = 4, 16^3  152 / 121 / 104
+//         p = 3, 16^3   84 /  66 /  58   p = 5, 13^3  147 / 121 / 124
+// FP32, p = 6 (11^3): 179 and, two lanes, 181, but 124 with one lane and two waves;
+// p = 1 (40^3) 93 and 111.
+template <int P, typename R>
+struct BwLanes {
+  static constexpr bool F64 = sizeof(R) == 8;
+  static constexpr int H = F64 || P == 1 || P == 6 ? 1 : 2;
+  static constexpr int WPS = F64 || P == 1 ? 1 : P == 3 || P == 4 ? 3 : 2;
+};
 // Compact index of stencil entry (vertex (x,y,z), offset (dx,dy,dz)) inside
 // the element table: rows in lexicographic order, each row's valid offsets in
 // (dz, dy, dx) lexicographic order.
@@ -90,17 +112,19 @@ __device__ __forceinline__ int compact_index(int x, int y, int z, int dx, int dy
   return rbase + ((dz + (z > 0 ? 1 : 0)) * ny + (dy + (y > 0 ? 1 : 0))) * nx + (dx + (x > 0 ? 1 : 0));
 }
 
-template <int P, typename T, typename R>
-__global__ __launch_bounds__(BwCfg<P>::THREADS, (BwOcc<R>::WPE)) void k_h1_backward(
+template <int P, typename T, typename R, int H>
+__global__ __launch_bounds__((BwCfg<P>::LANES * H), (BwLanes<P, R>::WPS)) void k_h1_backward(
     int64_t nel, int32_t chunk, const int32_t* __restrict__ elem_dofs, const double* __restrict__ coords,
     const T* __restrict__ kappa, T beta, const int32_t* __restrict__ row_ptr, const uint8_t* __restrict__ tables,
     const int32_t* __restrict__ elem_class, int64_t tab_stride, const uint16_t* __restrict__ ent_row, int batch,
     int64_t nnz, const T* __restrict__ gvals, T* __restrict__ gkappa, double* __restrict__ ework) {
   using C = BwCfg<P>;
   constexpr int Q = C::Q, NSUB = C::NSUB, NLOC = C::NLOC, NENT = C::NENT, NENTP = C::NENTP, E = C::E;
-  constexpr int TH = C::THREADS, TWE = C::TWE;
+  constexpr int LANES = C::LANES, TH = LANES * H, TWE = C::TWE;
   constexpr int NJ = (E * NENT + TH - 1) / TH;            // gathered entries per lane
-  constexpr int GW = E * NENT > 3 * E * 8 * NSUB ? E * NENT : 3 * E * 8 * NSUB;
+  constexpr int XW = 3 * E * 8 * NSUB;                    // corner adjoints
+  constexpr int HW = H > 1 ? XW + 36 * LANES : XW;        // and what lane 1 hands to lane 0
+  constexpr int GW = E * NENT > HW ? E * NENT : HW;
   // coordinates by component ([d][element vertex]): lanes reading the same
   // corner of neighbouring subelements then hit consecutive words
   __shared__ double sX[3 * E * NLOC];
@@ -110,6 +134,7 @@ __global__ __launch_bounds__(BwCfg<P>::THREADS, (BwOcc<R>::WPE)) void k_h1_backw
   // arithmetic's precision (both are R values), which halves this buffer in
   // the FP32 form
   __shared__ R sGX[GW];
+  __shared__ R sGk[H > 1 ? LANES : 1];  // the second lane's part of dL/dkappa
   const uint8_t* sTab = reinterpret_cast<const uint8_t*>(sTabW);
   R* sG = sGX;
   R* sXb = sGX;
@@ -193,9 +218,11 @@ __global__ __launch_bounds__(BwCfg<P>::THREADS, (BwOcc<R>::WPE)) void k_h1_backw
       gpos[j] = sRp[el * NLOC + gpos[j]] + (sTab[el * NENTP + (i2 - el * NENT)] & kRankMask);
     }
 
-    const bool act = tid < ne * NSUB;
-    const int el = act ? tid / NSUB : 0;
-    const int s = act ? tid - el * NSUB : 0;
+    const int half = H > 1 ? __builtin_amdgcn_readfirstlane(tid / LANES) : 0;
+    const int ct = tid - half * LANES;  // the lane's subelement
+    const bool act = ct < ne * NSUB;
+    const int el = act ? ct / NSUB : 0;
+    const int s = act ? ct - el * NSUB : 0;
     const int64_t e = e0 + el;
     const int si = s % P, sj = (s / P) % P, sk = s / (P * P);
     auto edges = [&](R (&ex)[2][2][3], R (&ey)[2][2][3], R (&ez)[2][2][3]) {
@@ -208,104 +235,150 @@ __global__ __launch_bounds__(BwCfg<P>::THREADS, (BwOcc<R>::WPE)) void k_h1_backw
       }
       h1_edges<R>(X, ex, ey, ez);
     };
-    R Kt[36], Wk[36], Wm[36];
-#pragma unroll
-    for (int i = 0; i < 36; ++i) Kt[i] = Wk[i] = Wm[i] = R(0);
-    if (act) {
-      R ex[2][2][3], ey[2][2][3], ez[2][2][3];
-      edges(ex, ey, ez);
-      H1Factors<R> F;
-      (void)h1_factors<R>(ex, ey, ez, R(1), R(0), F);
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-#pragma unroll
-        for (int v = u; v < 8; ++v) Kt[pair_index(u, v)] = h1_entry<R>(F, u, v);
-    }
-    // compact index of the 64 ordered corner pairs inside the element's table,
-    // two 16-bit indices per register, the same for every batch entry
-    uint32_t kpair[32];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int x = si + (u & 1), y = sj + ((u >> 1) & 1), z = sk + (u >> 2);
-#pragma unroll
-      for (int v = 0; v < 8; v += 2) {
-        const uint32_t i0 = static_cast<uint32_t>(
-            compact_index<P>(x, y, z, (v & 1) - (u & 1), ((v >> 1) & 1) - ((u >> 1) & 1), (v >> 2) - (u >> 2)));
-        const uint32_t i1 = static_cast<uint32_t>(compact_index<P>(
-            x, y, z, ((v + 1) & 1) - (u & 1), (((v + 1) >> 1) & 1) - ((u >> 1) & 1), ((v + 1) >> 2) - (u >> 2)));
-        kpair[(u * 8 + v) / 2] = i0 | (i1 << 16);
-      }
-    }
-    // the group's cotangent entries in compact (row-contiguous) order and the
-    // lane's coefficient: those of the next batch entry are loaded before this
-    // entry's compute (unconditionally: the last entry reloads itself), so
-    // that their latency is hidden behind it
     const int64_t kofs = e * NSUB + s;
-    T gv[NJ];
-    T kn;
+    // everything between the staging and the vertex sums, for the pairs of lane h
+    auto cells = [&](auto half_t) {
+      constexpr int h = decltype(half_t)::value;
+      R Kt[36], Wk[36], Wm[36];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) gv[j] = gvals[gpos[j]];
-    kn = kappa[kofs];
-    for (int b = 0; b < batch; ++b) {
-      lds_barrier();  // the previous entry of the batch has been consumed
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int i = tid + j * TH;
-        if (i < ne * NENT) sG[i] = static_cast<R>(gv[j]);
-      }
-      const R kb = static_cast<R>(kn);
-      {
-        const int bn = b + 1 < batch ? b + 1 : b;
-        const T* gn = gvals + static_cast<int64_t>(bn) * nnz;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) gv[j] = gn[gpos[j]];
-        kn = kappa[static_cast<int64_t>(bn) * nel * NSUB + kofs];
-      }
-      lds_barrier();
+      for (int i = 0; i < 36; ++i) Kt[i] = Wk[i] = Wm[i] = R(0);
       if (act) {
-        const R* ge = sG + el * NENT;
-        R gk = R(0);
-        // ordered pairs (u, v) and (v, u) both feed the unique entry {u, v};
-        // the 8 entries of a corner row are read first, so that the LDS reads
-        // overlap instead of each waiting for the previous one
+        R ex[2][2][3], ey[2][2][3], ez[2][2][3];
+        edges(ex, ey, ez);
+        H1Factors<R> F;
+        (void)h1_factors<R>(ex, ey, ez, R(1), R(0), F);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          R w[8];
+        for (int u = 0; u < 8; ++u)
 #pragma unroll
-          for (int v = 0; v < 8; ++v) {
-            const uint32_t kp = kpair[(u * 8 + v) / 2];
-            w[v] = ge[(v & 1) ? (kp >> 16) : (kp & 0xFFFFu)];
-          }
-          __builtin_amdgcn_sched_barrier(0);  // keep the 8 reads ahead of their uses
+          for (int v = u; v < 8; ++v)
+            if (pair_of<H>(h, u)) Kt[pair_index(u, v)] = h1_entry<R>(F, u, v);
+      }
+      // compact index of the ordered corner pairs (u, v) and (u, v + 1), v even:
+      // they are neighbours in corner u's row; the same for every batch entry
+      int kpair[32];
 #pragma unroll
-          for (int v = 0; v < 8; ++v) {
-            gk += Kt[pair_index(u, v)] * w[v];
-            Wk[pair_index(u, v)] += kb * w[v];
-            Wm[pair_index(u, v)] += w[v];
+      for (int u = 0; u < 8; ++u) {
+        const int x = si + (u & 1), y = sj + ((u >> 1) & 1), z = sk + (u >> 2);
+#pragma unroll
+        for (int v = 0; v < 8; v += 2)
+          kpair[(u * 8 + v) / 2] = el * NENT + compact_index<P>(x, y, z, -(u & 1), ((v >> 1) & 1) - ((u >> 1) & 1),
+                                                                (v >> 2) - (u >> 2));
+      }
+      // the group's cotangent entries in compact (row-contiguous) order and the
+      // lane's coefficient: those of the next batch entry are loaded before this
+      // entry's compute (unconditionally: the last entry reloads itself), so
+      // that their latency is hidden behind it
+      T gv[NJ];
+      T kn;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) gv[j] = gvals[gpos[j]];
+      kn = kappa[kofs];
+      R gk = R(0);
+      // dL/dkappa of batch entry b: this lane's part and the other's (written
+      // before the last barrier)
+      auto put_gk = [&](int b) {
+        if (h == 0 && act)
+          gkappa[static_cast<int64_t>(b) * nel * NSUB + kofs] = static_cast<T>(H > 1 ? gk + sGk[ct] : gk);
+      };
+      for (int b = 0; b < batch; ++b) {
+        lds_barrier();  // the previous entry of the batch has been consumed
+        if (b > 0) put_gk(b - 1);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const int i = tid + j * TH;
+          if (i < ne * NENT) sG[i] = static_cast<R>(gv[j]);
+        }
+        const R kb = static_cast<R>(kn);
+        {
+          const int bn = b + 1 < batch ? b + 1 : b;
+          const T* gn = gvals + static_cast<int64_t>(bn) * nnz;
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) gv[j] = gn[gpos[j]];
+          kn = kappa[static_cast<int64_t>(bn) * nel * NSUB + kofs];
+        }
+        lds_barrier();
+        gk = R(0);
+        if (act) {
+          // (u, v) and (v, u) both feed the unique entry {u, v}; the entries of a
+          // corner's row and column are read ahead of their uses, so that the LDS
+          // reads overlap
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            if (!pair_of<H>(h, u)) continue;
+            R w[8], wt[8];
+#pragma unroll
+            for (int v = u; v < 8; ++v) {
+              w[v] = sG[kpair[(u * 8 + (v & ~1)) / 2] + (v & 1)];
+              if (v > u) wt[v] = sG[kpair[(v * 8 + (u & ~1)) / 2] + (u & 1)];
+            }
+            if constexpr (P > 1) __builtin_amdgcn_sched_barrier(0);  // (p = 1 would spill)
+#pragma unroll
+            for (int v = u; v < 8; ++v) {
+              const int i = pair_index(u, v);
+              const R t = v == u ? w[v] : w[v] + wt[v];
+              gk += Kt[i] * t;
+              if constexpr (std::is_same<R, double>::value) {
+                Wk[i] += kb * t;
+                Wm[i] += t;
+              } else {  // FP32: one after the other, without the rounding of t
+                Wk[i] += kb * w[v];
+                Wm[i] += w[v];
+                if (v > u) {
+                  Wk[i] += kb * wt[v];
+                  Wm[i] += wt[v];
+                }
+              }
+            }
           }
         }
-        gkappa[static_cast<int64_t>(b) * nel * NSUB + kofs] = static_cast<T>(gk);
+        if (h == 1) sGk[ct] = gk;
       }
-    }
-    __syncthreads();  // sG is reused for the corner adjoints
-    if (act) {
-      R ex[2][2][3], ey[2][2][3], ez[2][2][3];
-      edges(ex, ey, ez);
-      R gx[2][2][3], gy[2][2][3], gz[2][2][3];
-      h1_adjoint<R>(ex, ey, ez, Wk, Wm, static_cast<R>(beta), gx, gy, gz);
-      // corner adjoints from the edge adjoints: e = X(hi) - X(lo)
-      R* xb = sXb + el * 24 * NSUB + s;
+      __syncthreads();  // sG is reused for the corner adjoints
+      put_gk(batch - 1);
+      if constexpr (H > 1) {
+        // lane 0 takes the adjoint of all pairs through the geometry
+        R* other = sGX + XW + ct;
 #pragma unroll
-      for (int v = 0; v < 8; ++v) {
-        const int a = v & 1, b2 = (v >> 1) & 1, c = v >> 2;
+        for (int u = 0; u < 8; ++u)
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          const R val = (a ? gx[b2][c][d] : -gx[b2][c][d]) + (b2 ? gy[a][c][d] : -gy[a][c][d]) +
-                        (c ? gz[a][b2][d] : -gz[a][b2][d]);
-          xb[(v * 3 + d) * NSUB] = val;
+          for (int v = u; v < 8; ++v)
+            if (h == 1 && pair_of<H>(1, u)) {
+              other[2 * pair_slot(u, v) * LANES] = Wk[pair_index(u, v)];
+              other[(2 * pair_slot(u, v) + 1) * LANES] = Wm[pair_index(u, v)];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+          for (int v = u; v < 8; ++v)
+            if (h == 0 && pair_of<H>(1, u)) {
+              Wk[pair_index(u, v)] = other[2 * pair_slot(u, v) * LANES];
+              Wm[pair_index(u, v)] = other[(2 * pair_slot(u, v) + 1) * LANES];
+            }
+      }
+      if (h == 0 && act) {
+        R ex[2][2][3], ey[2][2][3], ez[2][2][3];
+        edges(ex, ey, ez);
+        R gx[2][2][3], gy[2][2][3], gz[2][2][3];
+        h1_adjoint<R>(ex, ey, ez, Wk, Wm, static_cast<R>(beta), gx, gy, gz);
+        // corner adjoints from the edge adjoints: e = X(hi) - X(lo)
+        R* xb = sXb + el * 24 * NSUB + s;
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+          const int a = v & 1, b2 = (v >> 1) & 1, c = v >> 2;
+#pragma unroll
+          for (int d = 0; d < 3; ++d) {
+            const R val = (a ? gx[b2][c][d] : -gx[b2][c][d]) + (b2 ? gy[a][c][d] : -gy[a][c][d]) +
+                          (c ? gz[a][b2][d] : -gz[a][b2][d]);
+            xb[(v * 3 + d) * NSUB] = val;
+          }
         }
       }
-    }
+    };
+    if (half == 0)
+      cells(std::integral_constant<int, 0>{});
+    else
+      cells(std::integral_constant<int, H - 1>{});
     __syncthreads();
     // per element vertex: sum its <= 8 subelement corners in a fixed order
     for (int i = tid; i < ne * NLOC; i += TH) {
@@ -359,7 +432,8 @@ static int launch_bw(const lor_sched* sched, int batch, const int32_t* elem_dofs
   const int64_t nel = sched->nel;
   const int32_t chunk = C::E;  // one group of E elements per workgroup
   double* ework = static_cast<double*>(workspace);
-  k_h1_backward<P, T, R><<<static_cast<unsigned>(ceil_div(nel, chunk)), C::THREADS, 0, st>>>(
+  constexpr int H = BwLanes<P, R>::H;
+  k_h1_backward<P, T, R, H><<<static_cast<unsigned>(ceil_div(nel, chunk)), C::LANES * H, 0, st>>>(
       nel, chunk, elem_dofs, coords, static_cast<const T*>(kappa), static_cast<T>(beta), row_ptr, tab,
       dev_at<int32_t>(sched, sched->off_class), sched->tab_stride, dev_at<uint16_t>(sched, sched->off_ent_row),
       batch, sched->nnz, static_cast<const T*>(gvals), static_cast<T*>(gkappa), ework);

@@ -1,0 +1,30 @@
+"""The backward kernel in each of its forms (one or two lanes per subelement by
+degree and type), with element groups that are not full and batches of 1 to 5,
+against the oracle's autograd."""
+import pytest
+import torch
+
+import meshgen
+import paper_2210_12253_amd as lor
+from oracle import lor_oracle as orc
+from tests.test_gpu_backward import DEV, _gpu_grads, _rel, _rowwise, oracle_loss_grads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("batch", [1, 2, 5])
+@pytest.mark.parametrize("p", [1, 2, 3, 4, 5, 6])
+def test_all_degrees(p, batch):
+    m = meshgen.tri_split_mesh(2, 3, p, 0.1)
+    kap = meshgen.kappa_field(m["nel"], p, 1.0, seed=3, batch=batch)
+    rp, ci, _ = orc.h1_matrix(m["coords"], m["elem_dofs"], p, kap[0].detach(), 0.7)
+    cot = meshgen.cotangent(batch, rp[-1].item(), seed=1)
+    gk_ref, gx_ref = oracle_loss_grads(m, p, kap, 0.7, cot, rp, ci)
+    pat = lor.lor_pattern(lor.LOR_H1, p, torch.from_numpy(m["elem_dofs"]).to(DEV), m["ndofs"])
+    gk, gx = _gpu_grads(pat, m, kap, 0.7, cot, torch.float64)
+    assert _rowwise(gk, gk_ref) <= 1e-10 and _rowwise(gx, gx_ref) <= 1e-10
+    for _ in range(2):
+        gk32, gx32 = _gpu_grads(pat, m, kap, 0.7, cot, torch.float32)
+        assert _rel(gk32, gk_ref) <= 1e-5 and _rel(gx32, gx_ref) <= 1e-5
+    again = _gpu_grads(pat, m, kap, 0.7, cot, torch.float32)
+    assert torch.equal(again[0], gk32) and torch.equal(again[1], gx32)
