@@ -218,8 +218,8 @@ TRAFFIC_FILE = "h1_p6_32cubed_traffic.json"
 VALU_FILE = "h1_p6_32cubed_valu.json"
 # the headline kernels: rocprofv3 names -> keys of the committed records
 KERNELS = {
-    "owner_f64": "k_h1_owner<6, double, double>",
-    "owner_f32": "k_h1_owner<6, float, float>",
+    "owner_f64": "k_h1_owner<6, double, double, 16>",
+    "owner_f32": "k_h1_owner<6, float, float, 16>",
     "colored_f64": "k_h1_assemble<6, double, double>",
     "colored_f32": "k_h1_assemble<6, float, float>",
 }
@@ -228,8 +228,8 @@ KERNELS = {
 PROFILE_SETS = {
     "h1_p6_32cubed": (KERNELS, KERNEL_SOURCES),
     "backward_p4_16cubed_b8": ({
-        "backward_f64": "k_h1_backward<4, double, double>",
-        "backward_f32": "k_h1_backward<4, float, float>",
+        "backward_f64": "k_h1_backward<4, double, double, 1>",
+        "backward_f32": "k_h1_backward<4, float, float, 2>",
         "gather_vertices": "k_gather_vertices",
     }, ("lor_backward.hip", "lor_h1_adjoint.hpp", "lor_h1_math.hpp", "lor_common.hpp")),
     "h1_2d_p6_512sq": ({

@@ -103,8 +103,8 @@ __host__ __device__ __forceinline__ int64_t box_row_start(int64_t X, int64_t Y, 
 // with the fewest (*steps) is taken, so that neither the last round nor, on a small
 // mesh, the chip is left mostly idle.  `tiles`: waves per segment (all batch
 // entries).  Short segments are what a small mesh needs: H1 p = 2 on 4^3
-// elements (4 tiles) takes 48 us as segments of 8 layers and 11 us of 1 layer,
-// p = 5 on 13 x 9 x 11 47.7 us of 8 and 30.1 us of 4.
+// elements (4 tiles) takes 48 us as segments of 8 layers and 12.5 us of 1 layer (most
+// of it the launch), p = 5 on 13 x 9 x 11 47.7 us of 8 and 25.0 us of 4.
 inline int64_t march_segment(int64_t layers, int64_t tiles, int64_t slots, int64_t extra, int64_t* steps = nullptr) {
   constexpr int64_t kMaxSegments = 65535;  // second grid dimension
   int64_t seglen = layers, best = -1;
