@@ -49,11 +49,6 @@ struct DevBuf {
   int alloc(size_t bytes, hipStream_t stream) {
     if (bytes == 0) bytes = 16;
     st = stream;
-    // the calls read their results back, so they cannot be part of a graph
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    LOR_HIP(hipStreamIsCapturing(stream, &cap));
-    if (cap != hipStreamCaptureStatusNone)
-      LOR_FAIL(LOR_EDEVICE, "a pattern cannot be built on a stream under capture");
     hipError_t e = hipMallocAsync(&p, bytes, stream);
     if (e != hipSuccess) {
       p = nullptr;
@@ -2102,6 +2097,12 @@ extern "C" int lor_pattern(int space, int p, int64_t nel, int64_t nrows, const i
     lor_sched probe = *sched;
     if (layout(&probe, ref) != sched->dev_bytes) LOR_FAIL(LOR_EINVAL, "sched->dev_bytes changed since phase 1");
   }
+
+  // the phases read counts back, so they cannot be part of a graph
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  LOR_HIP(hipStreamIsCapturing(st, &capture));
+  if (capture != hipStreamCaptureStatusNone)
+    LOR_FAIL(LOR_EDEVICE, "a pattern cannot be built on a stream under capture");
 
   // temporaries of a phase, in one allocation
   Arena a;

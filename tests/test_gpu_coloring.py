@@ -61,3 +61,23 @@ def test_colours_are_sequential_greedy(space, mesh):
     ref = _greedy(em)
     assert np.array_equal(np.frombuffer(raw.tobytes(), dtype=np.int32), ref)
     assert pat.ncolors == ref.max() + 1
+
+
+def test_refused_under_capture():
+    """The pattern calls read counts back: on a stream under capture they fail
+    before they queue anything, and work as before afterwards."""
+    m = meshgen.tri_split_mesh(2, 3, 2, 0.1)
+    ed = torch.from_numpy(m["elem_dofs"]).to(DEV)
+    want = lor.lor_pattern(lor.LOR_H1, 2, ed, m["ndofs"])
+    torch.cuda.synchronize()
+    g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        g.capture_begin()
+        try:
+            with pytest.raises(lor.LorError):
+                lor.lor_pattern(lor.LOR_H1, 2, ed, m["ndofs"])
+        finally:
+            g.capture_end()
+    torch.cuda.synchronize()
+    again = lor.lor_pattern(lor.LOR_H1, 2, ed, m["ndofs"])
+    assert torch.equal(want.row_ptr, again.row_ptr) and torch.equal(want.col_idx, again.col_idx)
