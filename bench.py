@@ -228,8 +228,8 @@ KERNELS = {
 PROFILE_SETS = {
     "h1_p6_32cubed": (KERNELS, KERNEL_SOURCES),
     "backward_p4_16cubed_b8": ({
-        "backward_f64": "k_h1_backward<4, double, double, 1>",
-        "backward_f32": "k_h1_backward<4, float, float, 2>",
+        "backward_f64": "k_h1_backward<4, double, double, 1, 1>",
+        "backward_f32": "k_h1_backward<4, float, float, 2, 1>",
         "gather_vertices": "k_gather_vertices",
     }, ("lor_backward.hip", "lor_h1_adjoint.hpp", "lor_h1_math.hpp", "lor_common.hpp")),
     "h1_2d_p6_512sq": ({

@@ -54,7 +54,7 @@ int check_sched(const lor_sched* s, int space, int p, int64_t nel, int64_t nrows
 // subelements allow: E p^3 <= 64 lanes), one workgroup per group, so that
 // several independent workgroups share a CU and hide each other's latency
 // (gathers of coordinates and cotangents, LDS round trips).
-template <int P>
+template <int P, int ELEMS>
 struct BwCfg {
   static constexpr int Q = P + 1;
   static constexpr int NSUB = P * P * P;
@@ -62,7 +62,7 @@ struct BwCfg {
   static constexpr int T1 = 3 * P + 1;
   static constexpr int NENT = T1 * T1 * T1;
   static constexpr int NENTP = (NENT + 15) / 16 * 16;
-  static constexpr int E = NSUB >= 64 ? 1 : 64 / NSUB;
+  static constexpr int E = ELEMS;
   static constexpr int LANES = (E * NSUB + 63) / 64 * 64;  // one per subelement
   static constexpr int TWE = NENTP / 4;
 };
@@ -98,6 +98,15 @@ struct BwLanes {
   static constexpr bool F64 = sizeof(R) == 8;
   static constexpr int H = F64 || P == 1 || P == 6 ? 1 : 2;
   static constexpr int WPS = F64 || P == 1 ? 1 : P == 3 || P == 4 ? 3 : 2;
+  // Elements per group.  At p = 1 not one per lane: a group's entries are gathered by
+  // all lanes, 64 per element, and with 64 elements those in flight fill the
+  // registers (40^3, batch 8, FP64 and FP32, us: 64 elements 136 and 92, 32 121 and
+  // 88, 16 133 and 79; 60^3 376, 297, 376 and 214, 215, 204).
+  static constexpr int E = P == 1 ? (F64 ? 32 : 16) : P == 2 ? 8 : P == 3 ? 2 : 1;
+  // Half of that on a mesh whose groups are all resident at once even so: what a
+  // group gathers in a row is then half as long (p = 1, 8^3 35 -> 29 us; p = 2, 4^3 36
+  // -> 31, but 20^3 90 -> 95).
+  static constexpr int ESMALL = P == 1 ? 16 : P == 2 ? 4 : 1;
 };
 // Compact index of stencil entry (vertex (x,y,z), offset (dx,dy,dz)) inside
 // the element table: rows in lexicographic order, each row's valid offsets in
@@ -112,13 +121,13 @@ __device__ __forceinline__ int compact_index(int x, int y, int z, int dx, int dy
   return rbase + ((dz + (z > 0 ? 1 : 0)) * ny + (dy + (y > 0 ? 1 : 0))) * nx + (dx + (x > 0 ? 1 : 0));
 }
 
-template <int P, typename T, typename R, int H>
-__global__ __launch_bounds__((BwCfg<P>::LANES * H), (BwLanes<P, R>::WPS)) void k_h1_backward(
+template <int P, typename T, typename R, int H, int ELEMS>
+__global__ __launch_bounds__((BwCfg<P, ELEMS>::LANES * H), (BwLanes<P, R>::WPS)) void k_h1_backward(
     int64_t nel, int32_t chunk, const int32_t* __restrict__ elem_dofs, const double* __restrict__ coords,
     const T* __restrict__ kappa, T beta, const int32_t* __restrict__ row_ptr, const uint8_t* __restrict__ tables,
     const int32_t* __restrict__ elem_class, int64_t tab_stride, const uint16_t* __restrict__ ent_row, int batch,
     int64_t nnz, const T* __restrict__ gvals, T* __restrict__ gkappa, double* __restrict__ ework) {
-  using C = BwCfg<P>;
+  using C = BwCfg<P, ELEMS>;
   constexpr int Q = C::Q, NSUB = C::NSUB, NLOC = C::NLOC, NENT = C::NENT, NENTP = C::NENTP, E = C::E;
   constexpr int LANES = C::LANES, TH = LANES * H, TWE = C::TWE;
   constexpr int NJ = (E * NENT + TH - 1) / TH;            // gathered entries per lane
@@ -421,23 +430,48 @@ __global__ void k_gather_vertices(const int32_t* __restrict__ inc_ptr, const int
   gcoords[3 * g + 2] = a2;
 }
 
+static int num_cus_bw() {
+  static int cached[64] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  if (cached[dev] == 0) {
+    int n = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+    cached[dev] = n;
+  }
+  return cached[dev];
+}
+
 template <int P, typename T, typename R>
 static int launch_bw(const lor_sched* sched, int batch, const int32_t* elem_dofs, const double* coords,
                      const void* kappa, double beta, const int32_t* row_ptr, const void* gvals, void* gkappa,
                      double* gcoords, void* workspace, hipStream_t st) {
-  using C = BwCfg<P>;
-  if (sched->tab_stride != C::NENTP || sched->nent != C::NENT)
-    LOR_FAIL(LOR_EINVAL, "schedule tables do not match p = %d", P);
-  const uint8_t* tab = dev_at<uint8_t>(sched, sched->off_tables);
+  using L = BwLanes<P, R>;
   const int64_t nel = sched->nel;
-  const int32_t chunk = C::E;  // one group of E elements per workgroup
   double* ework = static_cast<double*>(workspace);
-  constexpr int H = BwLanes<P, R>::H;
-  k_h1_backward<P, T, R, H><<<static_cast<unsigned>(ceil_div(nel, chunk)), C::LANES * H, 0, st>>>(
-      nel, chunk, elem_dofs, coords, static_cast<const T*>(kappa), static_cast<T>(beta), row_ptr, tab,
-      dev_at<int32_t>(sched, sched->off_class), sched->tab_stride, dev_at<uint16_t>(sched, sched->off_ent_row),
-      batch, sched->nnz, static_cast<const T*>(gvals), static_cast<T*>(gkappa), ework);
-  LOR_LAUNCHED("k_h1_backward");
+  auto launch = [&](auto elems) -> int {
+    constexpr int E = decltype(elems)::value;
+    using C = BwCfg<P, E>;
+    if (sched->tab_stride != C::NENTP || sched->nent != C::NENT)
+      LOR_FAIL(LOR_EINVAL, "schedule tables do not match p = %d", P);
+    // one group of E elements per workgroup
+    k_h1_backward<P, T, R, L::H, E><<<static_cast<unsigned>(ceil_div(nel, E)), C::LANES * L::H, 0, st>>>(
+        nel, E, elem_dofs, coords, static_cast<const T*>(kappa), static_cast<T>(beta), row_ptr,
+        dev_at<uint8_t>(sched, sched->off_tables), dev_at<int32_t>(sched, sched->off_class), sched->tab_stride,
+        dev_at<uint16_t>(sched, sched->off_ent_row), batch, sched->nnz, static_cast<const T*>(gvals),
+        static_cast<T*>(gkappa), ework);
+    LOR_LAUNCHED("k_h1_backward");
+    return LOR_OK;
+  };
+  int rc;
+  if constexpr (L::ESMALL < L::E) {
+    const int64_t waves = ceil_div(nel, L::ESMALL) * (BwCfg<P, L::ESMALL>::LANES / 64 * L::H);
+    rc = waves <= static_cast<int64_t>(4 * L::WPS) * num_cus_bw() ? launch(std::integral_constant<int, L::ESMALL>{})
+                                                                  : launch(std::integral_constant<int, L::E>{});
+  } else {
+    rc = launch(std::integral_constant<int, L::E>{});
+  }
+  if (rc) return rc;
   k_gather_vertices<<<static_cast<unsigned>(ceil_div(sched->nrows, 256)), 256, 0, st>>>(
       dev_at<int32_t>(sched, sched->off_inc_ptr), dev_at<int32_t>(sched, sched->off_inc_list), sched->nrows, ework,
       gcoords);

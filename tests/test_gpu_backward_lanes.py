@@ -28,3 +28,19 @@ def test_all_degrees(p, batch):
         assert _rel(gk32, gk_ref) <= 1e-5 and _rel(gx32, gx_ref) <= 1e-5
     again = _gpu_grads(pat, m, kap, 0.7, cot, torch.float32)
     assert torch.equal(again[0], gk32) and torch.equal(again[1], gx32)
+
+
+@pytest.mark.parametrize("p,n", [(1, (27, 27, 27)), (2, (17, 17, 15)), (3, (13, 11, 11))])
+def test_full_groups_of_large_meshes(p, n):
+    """More elements than are resident at once in small groups: full-size groups,
+    the last one not full."""
+    m = meshgen.box_mesh(*n, p, 0.1)
+    kap = meshgen.kappa_field(m["nel"], p, 1.0, seed=3, batch=2)
+    rp, ci, _ = orc.h1_matrix(m["coords"], m["elem_dofs"], p, kap[0].detach(), 0.7)
+    cot = meshgen.cotangent(2, rp[-1].item(), seed=1)
+    gk_ref, gx_ref = oracle_loss_grads(m, p, kap, 0.7, cot, rp, ci)
+    pat = lor.lor_pattern(lor.LOR_H1, p, torch.from_numpy(m["elem_dofs"]).to(DEV), m["ndofs"])
+    gk, gx = _gpu_grads(pat, m, kap, 0.7, cot, torch.float64)
+    assert _rowwise(gk, gk_ref) <= 1e-10 and _rowwise(gx, gx_ref) <= 1e-10
+    gk32, gx32 = _gpu_grads(pat, m, kap, 0.7, cot, torch.float32)
+    assert _rel(gk32, gk_ref) <= 1e-5 and _rel(gx32, gx_ref) <= 1e-5
