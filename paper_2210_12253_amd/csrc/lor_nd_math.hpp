@@ -36,19 +36,25 @@ template <typename R>
 __device__ __forceinline__ bool nd_factors(const R (&ex)[2][2][3], const R (&ey)[2][2][3], const R (&ez)[2][2][3],
                                            R kap, R bet, H1Factors<R>& F, NDCurl<R>& W) {
   R c0[2][2][3], c1[2][2][3], c2[2][2][3];
-  // columns J / kGA2: det J = kGA2^3 det, r_a . r_b / det J = kGA2 (r_a . r_b / det),
-  // J_a . J_b / det J = (J_a . J_b / det) / kGA2
-  scaled_columns<R>(ex, c0);
-  scaled_columns<R>(ey, c1);
-  scaled_columns<R>(ez, c2);
+  // FP64: columns J / kGA2: det J = kGA2^3 det, r_a . r_b / det J = kGA2 (r_a . r_b / det),
+  // J_a . J_b / det J = (J_a . J_b / det) / kGA2.  FP32: J itself, for the constants that
+  // undo the scale would be rounded, and beta's part be off alike in every entry
+  constexpr bool kScaled = sizeof(R) == 8;
+  if constexpr (kScaled) {
+    scaled_columns<R>(ex, c0);
+    scaled_columns<R>(ey, c1);
+    scaled_columns<R>(ez, c2);
+  } else {
+    jac_columns<R>(ex, ey, ez, c0, c1, c2);
+  }
   R H00[2][2] = {}, H11[2][2] = {}, H22[2][2] = {};
   R Z01[2][2][2] = {}, Z02[2][2][2] = {};
   R G12q[2][2][2];
   R P00[2] = {}, P11[2] = {}, P22[2] = {};
   R P01[2][2] = {}, P02[2][2] = {}, P12[2][2] = {};
   bool ok = true;
-  const R wk = scale_by<R>(0.125 / kGA2, kap);
-  const R wb = scale_by<R>(0.125 * kGA2, bet);
+  const R wk = R(kScaled ? 0.125 / kGA2 : 0.125) * kap;
+  const R wb = R(kScaled ? 0.125 * kGA2 : 0.125) * bet;
 #pragma unroll
   for (int q3 = 0; q3 < 2; ++q3)
 #pragma unroll

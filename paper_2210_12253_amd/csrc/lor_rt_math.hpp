@@ -33,15 +33,22 @@ template <typename R>
 __device__ __forceinline__ bool rt_factors(const R (&ex)[2][2][3], const R (&ey)[2][2][3], const R (&ez)[2][2][3],
                                            R kap, R bet, RTFactors<R>& F) {
   R c0[2][2][3], c1[2][2][3], c2[2][2][3];
-  // columns J / kGA2: det J = kGA2^3 det, J_a . J_b / det J = (J_a . J_b / det) / kGA2
-  scaled_columns<R>(ex, c0);
-  scaled_columns<R>(ey, c1);
-  scaled_columns<R>(ez, c2);
+  // FP64: columns J / kGA2: det J = kGA2^3 det, J_a . J_b / det J = (J_a . J_b / det) / kGA2.
+  // FP32: J itself, for the constants that undo the scale would be rounded, and
+  // beta's part be off alike in every entry
+  constexpr bool kScaled = sizeof(R) == 8;
+  if constexpr (kScaled) {
+    scaled_columns<R>(ex, c0);
+    scaled_columns<R>(ey, c1);
+    scaled_columns<R>(ez, c2);
+  } else {
+    jac_columns<R>(ex, ey, ez, c0, c1, c2);
+  }
   R P00[2] = {}, P11[2] = {}, P22[2] = {};
   R P01[2][2] = {}, P02[2][2] = {}, P12[2][2] = {};
   R wsum = R(0);
   bool ok = true;
-  const R wb = scale_by<R>(0.125 / kGA2, bet);
+  const R wb = R(kScaled ? 0.125 / kGA2 : 0.125) * bet;
 #pragma unroll
   for (int q3 = 0; q3 < 2; ++q3)
 #pragma unroll
@@ -64,7 +71,7 @@ __device__ __forceinline__ bool rt_factors(const R (&ex)[2][2][3], const R (&ey)
         P02[q1][q3] += g * (A[0] * C[0] + A[1] * C[1] + A[2] * C[2]);
         P12[q2][q3] += g * (B[0] * C[0] + B[1] * C[1] + B[2] * C[2]);
       }
-  F.W = scale_by<R>(0.125 / (kGA2 * kGA2 * kGA2), kap) * wsum;
+  F.W = R(kScaled ? 0.125 / (kGA2 * kGA2 * kGA2) : 0.125) * kap * wsum;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     F.D00[a] = R(LL(a, 0)) * P00[0] + R(LL(a, 1)) * P00[1];

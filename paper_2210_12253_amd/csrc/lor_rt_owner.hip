@@ -24,9 +24,9 @@
 // What bounds it: one wave's step takes about 4 us, mostly the integration and the
 // latency between its phases, with two waves per SIMD (three spill: 67 us against
 // 50).  Barriers that wait for LDS only, lines addressed by one lane each instead
-// of by scalar arithmetic in every step (125 spilled scalars), columns by one
-// fused multiply-add per value and axis: p = 3, 24^3 56.7 -> 51.7 us, FP32 50.5 ->
-// 44.1, 7 x 7 x 8 14.7 -> 12.1.
+// of by scalar arithmetic in every step (125 spilled scalars), in FP64 columns by
+// one fused multiply-add per value and axis: p = 3, 24^3 56.7 -> 51.7 us, FP32 51.5
+// -> 46.3, 7 x 7 x 8 14.7 -> 12.1.
 //
 // Two distinct faces share at most one cell, so every off-diagonal entry has
 // one term and the matrix is bitwise symmetric; a diagonal entry takes its
