@@ -812,7 +812,8 @@ __global__ void k_max_row(const int32_t* __restrict__ row_ptr, int64_t nrows, in
   if ((threadIdx.x & 63) == 0) atomicMax(out, m);
 }
 
-// Every dof's incident elements must carry pairwise different colours.
+// Every dof's incident elements must carry pairwise different colours (those that
+// have one yet: it runs after each launch of the colouring).
 __global__ void k_check_colors(const int32_t* __restrict__ inc_ptr, const int32_t* __restrict__ inc_list,
                                int nloc, int64_t nrows, const int32_t* __restrict__ color,
                                int32_t* __restrict__ err) {
@@ -821,6 +822,7 @@ __global__ void k_check_colors(const int32_t* __restrict__ inc_ptr, const int32_
   const int32_t a = inc_ptr[g], b = inc_ptr[g + 1];
   for (int32_t i = a; i < b; ++i) {
     const int32_t ei = inc_list[i] / nloc;
+    if (color[ei] < 0) continue;
     for (int32_t j = i + 1; j < b; ++j) {
       const int32_t ej = inc_list[j] / nloc;
       if (ei != ej && color[ei] == color[ej]) {
