@@ -695,12 +695,16 @@ __global__ __launch_bounds__(THREADS) void k_row_cols(
 // is bounded all the same (`polls` iterations, then the wave leaves its
 // elements uncoloured and reports them in state[0] for the next launch, which
 // does at least the lowest of them), and waves that saw no progress sleep
-// between polls to leave the memory to those that do.
+// between polls to leave the memory to those that do.  Once some wave has given up,
+// waves without progress for kColIdle polls do too, instead of each waiting its
+// full time for elements that are left to the next launch anyway (400,000 elements
+// in a row: 430 ms, and 1,770 without).
 // 7,200 hexes of a triangle-split mesh (chain of 200): 6.1 ms as one launch
 // per step, 0.26 ms as one launch.
 constexpr int kColLanes = 8;
 constexpr int kColPend = 4;
 constexpr int kColPolls = 1 << 14;
+constexpr int kColIdle = 64;
 __global__ __launch_bounds__(256) void k_color_greedy(const int32_t* __restrict__ map, int nloc, int is_signed,
                                                       const int32_t* __restrict__ reps, int nreps,
                                                       const int32_t* __restrict__ inc_ptr,
@@ -778,6 +782,7 @@ __global__ __launch_bounds__(256) void k_color_greedy(const int32_t* __restrict_
     }
     if (!__ballot(live)) break;
     idle = __ballot(progress) ? 0 : idle + 1;
+    if (idle >= kColIdle && __hip_atomic_load(&state[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 0) break;
     if (idle > 4)
       __builtin_amdgcn_s_sleep(8);
     else if (idle > 0)

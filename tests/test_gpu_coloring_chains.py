@@ -2,6 +2,8 @@
 dependencies: a launch of the colouring ends with elements that still wait for
 uncoloured neighbours, and the next launches take them (one channel of elements
 for H(curl) and H(div), a narrow 2D strip, a long irregular extrusion for H1)."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -28,3 +30,20 @@ def test_long_chain(space):
     ref = _greedy(em)
     assert np.array_equal(np.frombuffer(raw.tobytes(), dtype=np.int32), ref)
     assert pat.ncolors == ref.max() + 1
+
+
+def test_time_grows_with_the_chain():
+    """Waves that cannot finish leave early instead of each waiting its full time:
+    a chain 6.7 times as long takes 6.7 times as long (24 times if they all wait)."""
+    def seconds(nel):
+        em, n = meshgen.nd_edge_map_box(nel, 1, 1, 1)
+        em = torch.from_numpy(em).to(DEV)
+        best = float("inf")
+        for _ in range(3):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            lor.lor_pattern(lor.LOR_ND, 1, em, n)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t)
+        return best
+    assert seconds(400000) < 12 * seconds(60000)
