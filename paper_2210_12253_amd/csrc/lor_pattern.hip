@@ -1524,9 +1524,27 @@ static int row_cols(bool full, const int32_t* map, int nloc, int is_signed, cons
 }
 
 // Box-lattice detection of an H1 mesh (see the box lattice kernels), first part:
-// the lattice strides from element 0 (scratch: four int32, device) and, if they
-// can be those of a box, its shape.  An error is returned only for device
-// failures.
+// whether the vertices that k_box_probe read can be those of a box, and its shape.
+static bool box_shape(const int32_t* h, int p, int64_t nel, int64_t nrows, BoxLattice* box) {
+  const int64_t q = p + 1;
+  const int64_t LX = static_cast<int64_t>(h[2]) - h[0], LXY = static_cast<int64_t>(h[3]) - h[0];
+  if (static_cast<int64_t>(h[1]) - h[0] != 1 || LX < q || LXY < LX * q || LXY % LX != 0 || nrows % LXY != 0)
+    return false;
+  const int64_t LY = LXY / LX, LZ = nrows / LXY;
+  if (LZ < q || (LX - 1) % p != 0 || (LY - 1) % p != 0 || (LZ - 1) % p != 0) return false;
+  const int64_t nx = (LX - 1) / p, ny = (LY - 1) / p, nz = (LZ - 1) / p;
+  if (nx * ny * nz != nel) return false;
+  box->LX = LX;
+  box->LY = LY;
+  box->LZ = LZ;
+  box->nx = static_cast<int>(nx);
+  box->ny = static_cast<int>(ny);
+  box->nz = static_cast<int>(nz);
+  return true;
+}
+
+// Both together (scratch: four int32, device).  An error is returned only for
+// device failures.
 static int probe_box(const int32_t* map, int p, int64_t nel, int64_t nrows, int32_t* scratch, hipStream_t st,
                      BoxLattice* box, bool* maybe) {
   *maybe = false;
@@ -1536,21 +1554,7 @@ static int probe_box(const int32_t* map, int p, int64_t nel, int64_t nrows, int3
   int32_t h[4];
   LOR_HIP(hipMemcpyAsync(h, scratch, sizeof(h), hipMemcpyDeviceToHost, st));
   LOR_HIP(hipStreamSynchronize(st));
-  const int64_t q = p + 1;
-  const int64_t LX = static_cast<int64_t>(h[2]) - h[0], LXY = static_cast<int64_t>(h[3]) - h[0];
-  if (static_cast<int64_t>(h[1]) - h[0] != 1 || LX < q || LXY < LX * q || LXY % LX != 0 || nrows % LXY != 0)
-    return LOR_OK;
-  const int64_t LY = LXY / LX, LZ = nrows / LXY;
-  if (LZ < q || (LX - 1) % p != 0 || (LY - 1) % p != 0 || (LZ - 1) % p != 0) return LOR_OK;
-  const int64_t nx = (LX - 1) / p, ny = (LY - 1) / p, nz = (LZ - 1) / p;
-  if (nx * ny * nz != nel) return LOR_OK;
-  box->LX = LX;
-  box->LY = LY;
-  box->LZ = LZ;
-  box->nx = static_cast<int>(nx);
-  box->ny = static_cast<int>(ny);
-  box->nz = static_cast<int>(nz);
-  *maybe = true;
+  *maybe = box_shape(h, p, nel, nrows, box);
   return LOR_OK;
 }
 
@@ -1923,13 +1927,16 @@ static size_t general_ws_bytes(int64_t nel, int64_t nrows, size_t nreps, int64_t
 }
 
 // What the host reads together in phase 2: error bits, elements left uncoloured,
-// highest colour, longest row, rows past the short form, table mismatch.
-enum { kErr, kLeft, kTop, kLong, kOvf, kMismatch, kState };
+// highest colour, longest row, rows past the short form, table mismatch, and the
+// four words of k_box_probe (H1).
+enum { kErr, kLeft, kTop, kLong, kOvf, kMismatch, kProbe, kState = kProbe + 4 };
 
 // Phase 2 on any mesh: greedy colouring, columns and rank tables from the
-// incidence lists, then one stored table per distinct table.
+// incidence lists, then one stored table per distinct table.  h: the state words
+// as last read.
 static int general_schedule(lor_sched* s, const RefElem& ref, int is_signed, const int32_t* map,
-                            const int32_t* row_ptr, int32_t* col_idx, int32_t* state, Arena& a, hipStream_t st) {
+                            const int32_t* row_ptr, int32_t* col_idx, int32_t* state, int32_t (&h)[kState], Arena& a,
+                            hipStream_t st) {
   const int64_t nel = s->nel, nrows = s->nrows;
   const int nloc = s->nloc;
   int32_t* d_color = dev_at<int32_t>(s, s->off_color);
@@ -1940,7 +1947,6 @@ static int general_schedule(lor_sched* s, const RefElem& ref, int is_signed, con
   const int32_t* d_st_ptr = dev_at<int32_t>(s, s->off_st_ptr);
   const int32_t* d_st_col = dev_at<int32_t>(s, s->off_st_col);
   int rc;
-  int32_t h[kState] = {};
   auto read_state = [&]() -> int {
     LOR_HIP(hipMemcpyAsync(h, state, sizeof(h), hipMemcpyDeviceToHost, st));
     LOR_HIP(hipStreamSynchronize(st));
@@ -2239,12 +2245,23 @@ extern "C" int lor_pattern(int space, int p, int64_t nel, int64_t nrows, const i
     }
     if (is_box && (rc = place_box(elem_map, p, nel, box, e3, a, st, &is_box))) return rc;
     if (!is_box) LOR_FAIL(LOR_EINVAL, "elem_map is not the one phase 1 saw");
+    if ((rc = box_schedule(sched, ref, box, elem_map, row_ptr, col_idx, d_err, a, st))) return rc;
+  } else {
+    const bool probe = space == LOR_H1 && nel > 0 && nrows >= 8;
+    if (probe) {
+      k_box_probe<<<1, 64, 0, st>>>(elem_map, p, d_err + kProbe);
+      LOR_LAUNCHED("k_box_probe");
+    }
+    int32_t h[kState] = {};
+    if ((rc = general_schedule(sched, ref, is_signed, elem_map, row_ptr, col_idx, d_err, h, a, st))) return rc;
+    // a box lattice now, but none in phase 1
+    if (probe && box_shape(h + kProbe, p, nel, nrows, &box)) {
+      int32_t* e3;
+      LOR_TAKE(e3, a, int32_t, nel);
+      if ((rc = place_box(elem_map, p, nel, box, e3, a, st, &is_box))) return rc;
+      if (is_box) LOR_FAIL(LOR_EINVAL, "elem_map is not the one phase 1 saw");
+    }
   }
-  if (is_box)
-    rc = box_schedule(sched, ref, box, elem_map, row_ptr, col_idx, d_err, a, st);
-  else
-    rc = general_schedule(sched, ref, is_signed, elem_map, row_ptr, col_idx, d_err, a, st);
-  if (rc) return rc;
   // a quadrilateral mesh keeps its general schedule (the coloured kernel) and
   // gains the owner-computes one if it is a 2D box lattice; an H(div) mesh
   // if its face map is a face lattice
