@@ -25,8 +25,9 @@
  *   - Every array argument is a DEVICE pointer (hipMalloc'd / torch CUDA memory)
  *     owned by the caller, except where a parameter says "host".  The library
  *     keeps no device memory between calls; lor_pattern allocates and frees its
- *     own temporaries in stream order (the device has them back at the stream's
- *     next synchronisation).
+ *     own temporaries (on an H1 box lattice the device has them back when the
+ *     call returns, on other meshes, where they are ordered on the stream, at the
+ *     stream's next synchronisation).
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     lor_pattern synchronises `stream` (it must read counts back); the
  *     lor_assemble_* calls are asynchronous on `stream` and never synchronise.

@@ -35,24 +35,29 @@ namespace lor {
 
 // ------------------------------------------------------------ device buffer
 
-// Temporary device memory of one call, ordered on its stream: allocated for the
-// work queued after it and given back once the work queued before the end of the
-// scope is done.  (The two arenas of a mesh of 7,200 elements, 19 and 9 MB, take
-// 20 us each where the driver has a freed block at hand and 300 where it has to map
-// one, which hipMalloc and hipFree made it do each time.)
+// Temporary device memory of one call.  On general meshes it is ordered on the
+// call's stream: allocated for the work queued after it and given back once the
+// work queued before the end of the scope is done.  (The two arenas of a mesh of
+// 7,200 elements, 19 and 9 MB, take 20 us each where the driver has a freed block at
+// hand and 300 where it has to map one, which hipMalloc and hipFree made it do each
+// time.)  The H1 lattice path needs little and has no other cost to hide it behind: an
+// ordered allocation takes 18 us, hipMalloc and hipFree of up to 1.5 MiB one
+// (pattern of 3^3 elements, p = 2: 357 and 311 us; 16^3, p = 4: 447 and 395).
 struct DevBuf {
   void* p = nullptr;
   hipStream_t st = nullptr;
+  bool ordered = false;
   ~DevBuf() {
-    if (p) (void)hipFreeAsync(p, st);
+    if (p) (void)(ordered ? hipFreeAsync(p, st) : hipFree(p));
   }
-  int alloc(size_t bytes, hipStream_t stream) {
+  int alloc(size_t bytes, hipStream_t stream, bool in_order) {
     if (bytes == 0) bytes = 16;
     st = stream;
-    hipError_t e = hipMallocAsync(&p, bytes, stream);
+    ordered = in_order;
+    hipError_t e = ordered ? hipMallocAsync(&p, bytes, stream) : hipMalloc(&p, bytes);
     if (e != hipSuccess) {
       p = nullptr;
-      set_error("hipMallocAsync(%zu) failed: %s", bytes, hipGetErrorString(e));
+      set_error("%s(%zu) failed: %s", ordered ? "hipMallocAsync" : "hipMalloc", bytes, hipGetErrorString(e));
       return LOR_EDEVICE;
     }
     return LOR_OK;
@@ -73,10 +78,10 @@ static size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255);
 struct Arena {
   DevBuf buf;
   size_t cap = 0, used = 0;
-  int alloc(size_t bytes, hipStream_t st) {
+  int alloc(size_t bytes, hipStream_t st, bool in_order) {
     cap = bytes;
     used = 0;
-    return buf.alloc(bytes, st);
+    return buf.alloc(bytes, st, in_order);
   }
   template <typename T>
   T* take(size_t count) {
@@ -2042,7 +2047,7 @@ static int general_schedule(lor_sched* s, const RefElem& ref, int is_signed, con
       DevBuf big;
       uint32_t* tmp = bytes <= kTableScratch ? a.take<uint32_t>(bytes / 4) : nullptr;
       if (!tmp) {
-        if ((rc = big.alloc(bytes, st))) return rc;
+        if ((rc = big.alloc(bytes, st, true))) return rc;
         tmp = big.as<uint32_t>();
       }
       k_table_gather<<<ceil_div(ncls * words, 256), 256, 0, st>>>(tabw, words, ncls, class_rep, tmp);
@@ -2130,7 +2135,7 @@ extern "C" int lor_pattern(int space, int p, int64_t nel, int64_t nrows, const i
     // (row_ptr serves as the probe's scratch: it is written below)
     if (space == LOR_H1 && (rc = probe_box(elem_map, p, nel, nrows, row_ptr, st, &box, &is_box))) return rc;
     if (is_box) {
-      if ((rc = a.alloc(arena_bytes<int32_t>(nel) + arena_bytes<int32_t>(1), st))) return rc;
+      if ((rc = a.alloc(arena_bytes<int32_t>(nel) + arena_bytes<int32_t>(1), st, false))) return rc;
       int32_t* e3;
       LOR_TAKE(e3, a, int32_t, nel);
       if ((rc = place_box(elem_map, p, nel, box, e3, a, st, &is_box))) return rc;
@@ -2147,7 +2152,7 @@ extern "C" int lor_pattern(int space, int p, int64_t nel, int64_t nrows, const i
       if ((rc = g.alloc(arena_bytes<int32_t>(2) + arena_bytes<int32_t>(nrows + 1) + arena_bytes<int32_t>(nel * nloc) +
                         2 * arena_bytes<int32_t>(nrows) + arena_bytes<int64_t>(nrows + 1) +
                         arena_bytes<int32_t>(stencil.size()) + std::max(incidence_ws_bytes(nrows), scan_ws_bytes(nrows)),
-                        st)))
+                        st, true)))
         return rc;
       int32_t *state, *inc_ptr, *inc_list, *cnt, *ovf, *st_ptr;
       int64_t* ptr64;
@@ -2208,12 +2213,11 @@ extern "C" int lor_pattern(int space, int p, int64_t nel, int64_t nrows, const i
   // ------------------------------------------------------------------ phase 2
   // (the lattice searches take two or three more small slices)
   const size_t search = 4 * arena_bytes<int32_t>(8) + arena_bytes<int32_t>(nel);
+  const bool box1 = sched->owner == 1 && space == LOR_H1;  // (a 2D box lattice is found in phase 2)
   if ((rc = a.alloc(arena_bytes<int32_t>(kState) + search +
                     std::max({incidence_ws_bytes(nrows), order_ws_bytes(nel) + arena_bytes<int32_t>(kBoxKeys),
-                              sched->owner == 1 && space == LOR_H1
-                                  ? 0
-                                  : general_ws_bytes(nel, nrows, ref.reps.size(), sched->tab_stride)}),
-                    st)))
+                              box1 ? 0 : general_ws_bytes(nel, nrows, ref.reps.size(), sched->tab_stride)}),
+                    st, !box1)))
     return rc;
   LOR_TAKE(d_err, a, int32_t, kState);  // error bits first
   k_fill_i32<<<1, 64, 0, st>>>(d_err, kState, 0);
@@ -2231,7 +2235,6 @@ extern "C" int lor_pattern(int space, int p, int64_t nel, int64_t nrows, const i
   if ((rc = build_incidence(elem_map, nel, nloc, is_signed, nrows, dev_at<int32_t>(sched, sched->off_inc_ptr),
                             dev_at<int32_t>(sched, sched->off_inc_list), d_err, a, st)))
     return rc;
-  const bool box1 = sched->owner == 1 && space == LOR_H1;  // (a 2D box lattice is found in phase 2)
   sched->owner = 0;
   sched->box[0] = sched->box[1] = sched->box[2] = 0;
   sched->max_row_nnz = 0;

@@ -1,5 +1,6 @@
 """The two phases of the pattern call: an element map that is not the one phase 1
-saw is refused also where its rows have the same lengths."""
+saw is refused also where its rows have the same lengths, and on a box lattice the
+temporaries are back when the call returns."""
 import ctypes
 
 import pytest
@@ -39,3 +40,21 @@ def test_other_map_is_refused():
         assert _phases(both, both, p, m["ndofs"])[:2] == (L.LOR_OK, L.LOR_OK)
     moved, _ = meshgen.permute_elements(m, seed=2)       # a lattice with its elements in any order stays one
     assert _phases(box, moved["elem_dofs"], p, m["ndofs"])[:2] == (L.LOR_OK, L.LOR_OK)
+
+
+def test_lattice_temporaries_are_back_at_return():
+    hip = ctypes.CDLL("libamdhip64.so")
+
+    def free():
+        a, b = ctypes.c_size_t(), ctypes.c_size_t()
+        assert hip.hipMemGetInfo(ctypes.byref(a), ctypes.byref(b)) == 0
+        return a.value
+    m = meshgen.box_mesh(48, 48, 48, 2)      # about 900,000 vertices: scratch of 10 MB
+    ed = torch.from_numpy(m["elem_dofs"]).to(DEV)
+    for _ in range(2):                       # torch's own blocks are there from the second time on
+        torch.cuda.synchronize()
+        before = free()
+        pat = L.lor_pattern(L.LOR_H1, 2, ed, m["ndofs"])
+        after = free()
+        del pat
+    assert after == before
