@@ -438,7 +438,8 @@ int lor_discrete_gradient(int p, int64_t nel, int64_t ndofs_h1, int64_t nedges, 
  *               z-faces at offset 2p^2(p+1), index i + p(j + p k) with k <= p;
  *               entry f >= 0 is face f with the local orientation, f < 0 is
  *               face -1-f with the opposite one.
- *   workspace   [nfaces] int32 device buffer (scratch: first incidence of every face).
+ *   workspace   [nfaces] int32 device buffer (first incidence of every face,
+ *               element * 3p^2(p+1) + local face; INT32_MAX for a face in no element).
  *   row_ptr     [nfaces+1] int32, col_idx [4*nfaces] int32, values [4*nfaces]
  *               in dtype: written.
  *   diag        NULL or device int32[2]: [0] += faces in no element (row of

@@ -117,7 +117,8 @@ __global__ __launch_bounds__(kAuxThreads) void k_discrete_gradient(
 // second pass is nearly all reads; an atomic minimum for every index took 22 us
 // and the fill before it 3 for 1.5 million indices, these take 7 and 9.
 // No fill: what the claim does not overwrite belongs to no element, and is found
-// out by the faces map, which does not name that face at that index.
+// out by the faces map, which does not name that face at that index (the curl kernel
+// marks it then).
 __global__ __launch_bounds__(kAuxThreads) void k_face_claim(const int32_t* __restrict__ elem_faces, int64_t total,
                                                             int64_t nfaces, int32_t* __restrict__ owner,
                                                             int32_t* __restrict__ diag) {
@@ -199,7 +200,7 @@ __device__ __forceinline__ void local_face_edges(int lf, int (&le)[4]) {
 template <int p, typename T>
 __global__ __launch_bounds__(kAuxThreads) void k_discrete_curl(
     int64_t nel, int64_t nfaces, int64_t nedges, const int32_t* __restrict__ elem_edges,
-    const int32_t* __restrict__ elem_faces, const int32_t* __restrict__ owner, int32_t* __restrict__ row_ptr,
+    const int32_t* __restrict__ elem_faces, int32_t* __restrict__ owner, int32_t* __restrict__ row_ptr,
     int32_t* __restrict__ col_idx, T* __restrict__ values, int32_t* __restrict__ diag) {
   constexpr int q = p + 1;
   constexpr int nlocf = 3 * p * p * q, nloce = 3 * p * q * q;
@@ -234,7 +235,10 @@ __global__ __launch_bounds__(kAuxThreads) void k_discrete_curl(
     if (f[j] >= nfaces) continue;
     row_ptr[f[j]] = static_cast<int32_t>(4 * f[j]);
     if (f[j] == nfaces - 1) row_ptr[nfaces] = static_cast<int32_t>(4 * nfaces);
-    none += mine[j] ? 0 : 1;  // face in no element: its row is left as four zeros at column 0
+    if (!mine[j]) {  // face in no element: its row is left as four zeros at column 0
+      ++none;
+      owner[f[j]] = INT32_MAX;
+    }
     const T sf = named[j] < 0 ? T(-1) : T(1);
     int32_t cols[4];
     T vals[4];
