@@ -76,9 +76,14 @@ typedef enum { LOR_DIAG_ONE = 0, LOR_DIAG_KEEP = 1, LOR_DIAG_ZERO = 2 } lor_diag
 /* lor_assemble_h1, lor_assemble_h1_2d, lor_assemble_rt and lor_assemble_nd:
  * kernel choice.  By default the owner-computes kernel runs when the schedule
  * has it (sched->owner); otherwise a kernel that sums row by row on small meshes
- * and the coloured kernel on large ones.  LOR_COLORED forces the coloured
+ * (not in 2D) and the coloured kernel on large ones.  LOR_COLORED forces the coloured
  * kernel, LOR_OWNER the owner-computes one (LOR_EUNSUPPORTED if the schedule has
- * none).  All give the same matrix up to the order of the floating-point sums. */
+ * none).  All give the same matrix up to rounding: they sum in different orders,
+ * and in the FP32 form the row-by-row kernel integrates in FP64 and rounds every
+ * entry once, while the coloured one integrates and adds up across elements in
+ * FP32.  The default counts the cells of all batch entries, so an entry of a large
+ * batch may come from another of them than the same entry assembled alone; with
+ * LOR_COLORED or LOR_OWNER its bits do not depend on the batch. */
 #define LOR_COLORED 0x2u
 #define LOR_OWNER 0x4u
 
@@ -197,8 +202,9 @@ int lor_pattern(int space, int p, int64_t nel, int64_t nrows, const int32_t* ele
  *   dtype          LOR_F64: all arithmetic in FP64.  LOR_F32: edge vectors
  *                  formed in FP64 then rounded; Jacobians, quadrature and
  *                  subelement matrices in FP32 (FP64 on flagged subelements if
- *                  flags has LOR_FP64_FALLBACK); sums within an element in FP64;
- *                  stored as FP32.
+ *                  flags has LOR_FP64_FALLBACK, and on all of them where the
+ *                  values are summed row by row); sums within an element in
+ *                  FP64; stored as FP32.
  *   flags          LOR_FP64_FALLBACK (FP32 only), and at most one of
  *                  LOR_COLORED / LOR_OWNER (kernel choice, see above).  The
  *                  owner-computes kernel sums every row once, whole, in FP64

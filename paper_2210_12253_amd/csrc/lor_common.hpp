@@ -124,7 +124,11 @@ inline int64_t march_segment(int64_t layers, int64_t tiles, int64_t slots, int64
 
 // Whether a mesh without an owner-computes schedule is assembled row by row:
 // up to `per_color` cells (all batch entries) per colour, and rows that fit 64 KB
-// of LDS (256 lanes, `lanes` per row; max_row_nnz 0: unknown).
+// of LDS (256 lanes, `lanes` per row; max_row_nnz 0: unknown).  The batch counts,
+// since it shares the launches per colour: by the mesh alone batches would be
+// slower (24,300 cells, p = 3, batch 8: H(curl) 219 -> 369 us in FP64, 159 -> 362 in
+// FP32; H1, batch 32: 224 -> 380).  So a batch can take another kernel than one of
+// its entries alone; LOR_COLORED gives both the same.
 inline bool rows_pay(const lor_sched* s, int64_t cells, int64_t per_color, int lanes) {
   const int row = (s->max_row_nnz > 0 ? s->max_row_nnz : LOR_MAX_ROW_NNZ) | 1;
   return cells <= per_color * s->ncolors && 256 / lanes * row * 8 <= 64 * 1024;

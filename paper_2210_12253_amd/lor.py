@@ -275,8 +275,9 @@ def lor_assemble_h1(pat: Pattern, elem_dofs, coords, kappa, beta: float, dtype=t
                     diag: torch.Tensor | None = None, out: torch.Tensor | None = None,
                     kernel: str = "auto") -> torch.Tensor:
     """Values of the H1 LOR matrix, [nnz] (or [batch, nnz] for kappa [batch, nel, p^3]).
-    kernel: "auto" (owner-computes where the schedule has it, else row by row on a
-    small mesh and coloured on a large one), "owner" or "colored"."""
+    kernel: "auto" (owner-computes where the schedule has it, else row by row where
+    mesh times batch is small and coloured elsewhere, which differ in rounding),
+    "owner" or "colored"."""
     if kernel not in _KERNEL_FLAGS:
         raise ValueError("kernel must be 'auto', 'owner' or 'colored'")
     lib = load_library()
@@ -305,8 +306,8 @@ def lor_assemble_nd(pat: Pattern, elem_dofs, elem_edges, coords, kappa, beta: fl
                     kernel: str = "auto") -> torch.Tensor:
     """Values of the H(curl) LOR matrix, [nnz] (or [batch, nnz]).  kernel:
     "auto" (owner-computes when the edge map is an edge lattice, else
-    row by row on a small mesh and coloured on a large one), "owner" or
-    "colored"."""
+    row by row where mesh times batch is small and coloured elsewhere, which
+    differ in rounding), "owner" or "colored"."""
     if kernel not in _KERNEL_FLAGS:
         raise ValueError("kernel must be 'auto', 'owner' or 'colored'")
     lib = load_library()
@@ -366,8 +367,8 @@ def lor_assemble_rt(pat: Pattern, elem_dofs, elem_faces, coords, kappa, beta: fl
                     kernel: str = "auto") -> torch.Tensor:
     """Values of the H(div) LOR matrix, [nnz] (or [batch, nnz]).  kernel:
     "auto" (owner-computes when the face map is a face lattice, else
-    row by row on a small mesh and coloured on a large one), "owner" or
-    "colored"."""
+    row by row where mesh times batch is small and coloured elsewhere, which
+    differ in rounding), "owner" or "colored"."""
     if kernel not in _KERNEL_FLAGS:
         raise ValueError("kernel must be 'auto', 'owner' or 'colored'")
     lib = load_library()
