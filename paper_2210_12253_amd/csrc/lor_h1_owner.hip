@@ -550,17 +550,15 @@ static int owner_num_cus() {
 }
 
 template <int P, typename T, typename R, int S>
-static int launch_owner_tile(const lor_sched* sched, int batch, const void* kappa, double beta, const double* coords,
-                             void* values, unsigned flags, double thr, int32_t* diag, hipStream_t st) {
+static int launch_owner_tile(const lor_sched* sched, int batch, int64_t seglen, const void* kappa, double beta,
+                             const double* coords, void* values, unsigned flags, double thr, int32_t* diag,
+                             hipStream_t st) {
   using C = OwnCfg<T, R, S>;
   const int nex = sched->box[0], ney = sched->box[1], nez = sched->box[2];
   const int NXc = nex * P, NYc = ney * P, NZc = nez * P;
   const int64_t ntx = ceil_div(NXc, C::STRIDE), nty = ceil_div(NYc, C::STRIDE);
   const int64_t tiles = ntx * nty;
   if (tiles > INT32_MAX) LOR_FAIL(LOR_EOVERFLOW, "too many owner-computes tiles");
-  // segments along z: one above the bottom integrates the layer below it too
-  const int64_t slots = static_cast<int64_t>(owner_num_cus()) * C::SLOTS;
-  const int64_t seglen = march_segment(NZc, tiles * batch, slots, 1);
   const int64_t nseg = ceil_div(NZc, seglen);
   dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>(nseg), static_cast<unsigned>(batch));
   k_h1_owner<P, T, R, S><<<grid, C::THREADS, 0, st>>>(
@@ -581,22 +579,24 @@ static int launch_owner(const lor_sched* sched, int batch, const void* kappa, do
     LOR_FAIL(LOR_EINVAL, "the owner-computes schedule does not describe the mesh");
   if (!owner_fits(sched, static_cast<int>(sizeof(T))))
     LOR_FAIL(LOR_EUNSUPPORTED, "owner-computes kernel: coordinates or coefficients span 4 GiB or more");
-  // The tile with fewer steps (rounds x layers per wave): on a large mesh 16 x 16,
+  // Segments along z (one above the bottom integrates the layer below it too), and the
+  // tile with fewer steps (rounds x layers per wave): on a large mesh 16 x 16,
   // which integrates 1.14 cells per row instead of 1.31 (p = 6, 32^3: 65 steps
   // against 80, 556 us against 583).  On equal numbers, as on small meshes, 8 x 8:
   // its waves wait for no barrier (p = 5, 13 x 9 x 11: 25.4 us against 26.2).
   const int64_t cus = owner_num_cus();
-  auto steps = [&](int64_t stride, int64_t slots) {
-    int64_t cost;
-    march_segment(static_cast<int64_t>(nez) * P, ceil_div(nex * P, stride) * ceil_div(ney * P, stride) * batch, slots, 1,
-                  &cost);
-    return cost;
+  auto segment = [&](int64_t stride, int64_t slots, int64_t* steps) {
+    return march_segment(static_cast<int64_t>(nez) * P,
+                         ceil_div(nex * P, stride) * ceil_div(ney * P, stride) * batch, slots, 1, steps);
   };
   using C8 = OwnCfg<T, T, 8>;
   using C16 = OwnCfg<T, T, 16>;
-  if (steps(C16::STRIDE, cus * C16::SLOTS) < steps(C8::STRIDE, cus * C8::SLOTS))
-    return launch_owner_tile<P, T, T, 16>(sched, batch, kappa, beta, coords, values, flags, thr, diag, st);
-  return launch_owner_tile<P, T, T, 8>(sched, batch, kappa, beta, coords, values, flags, thr, diag, st);
+  int64_t steps8, steps16;
+  const int64_t len8 = segment(C8::STRIDE, cus * C8::SLOTS, &steps8);
+  const int64_t len16 = segment(C16::STRIDE, cus * C16::SLOTS, &steps16);
+  if (steps16 < steps8)
+    return launch_owner_tile<P, T, T, 16>(sched, batch, len16, kappa, beta, coords, values, flags, thr, diag, st);
+  return launch_owner_tile<P, T, T, 8>(sched, batch, len8, kappa, beta, coords, values, flags, thr, diag, st);
 }
 
 // Values on a box lattice.  The rows start where the lattice puts them (the
