@@ -108,6 +108,23 @@ struct BwLanes {
   // -> 31, but 20^3 90 -> 95).
   static constexpr int ESMALL = P == 1 ? 16 : P == 2 ? 4 : 1;
 };
+
+// p = 1: groups of 64 elements (one per lane) where smaller ones are the slower, with
+// `round` the elements that these groups take in one round of the chip.  Us with 64
+// and with 32 (FP64) or 16 (FP32):
+//   a second round of smaller groups that is nearly empty, just above half a round:
+//     FP64 (to two thirds) 33^3 38 and 46, 35^3 40 and 46, batch 8 75 and 85, 81 and 86;
+//       37^3 59 and 48
+//     FP32 (to three fifths, small batches) 33^3 36 and 41, batch 4 43 and 48; 35^3 36
+//       and 37, batch 4 45 and 43
+//   large meshes in FP32 with little to gather per element: 57^3 96 and 108, 93^3 421
+//     and 486, batch 2 106 and 114, 462 and 506, but batch 4 129 and 128, batch 8, 79^3
+//     454 and 462; 54^3 87 and 90, batch 2 99 and 95
+inline bool bw_one_per_lane(bool f64, int64_t nel, int64_t round, int batch) {
+  if (2 * nel > round && (f64 ? 3 * nel <= 2 * round : 5 * nel <= 3 * round)) return f64 || batch <= 4;
+  return !f64 && batch <= 2 && 2 * nel > 5 * round;
+}
+
 // Compact index of stencil entry (vertex (x,y,z), offset (dx,dy,dz)) inside
 // the element table: rows in lexicographic order, each row's valid offsets in
 // (dz, dy, dx) lexicographic order.
@@ -463,14 +480,15 @@ static int launch_bw(const lor_sched* sched, int batch, const int32_t* elem_dofs
     LOR_LAUNCHED("k_h1_backward");
     return LOR_OK;
   };
+  const int64_t slots = static_cast<int64_t>(4 * L::WPS) * num_cus_bw();  // waves
+  const int64_t small = ceil_div(nel, L::ESMALL) * (BwCfg<P, L::ESMALL>::LANES / 64 * L::H);
   int rc;
-  if constexpr (L::ESMALL < L::E) {
-    const int64_t waves = ceil_div(nel, L::ESMALL) * (BwCfg<P, L::ESMALL>::LANES / 64 * L::H);
-    rc = waves <= static_cast<int64_t>(4 * L::WPS) * num_cus_bw() ? launch(std::integral_constant<int, L::ESMALL>{})
-                                                                  : launch(std::integral_constant<int, L::E>{});
-  } else {
+  if (P == 1 && bw_one_per_lane(L::F64, nel, 64 * slots, batch))
+    rc = launch(std::integral_constant<int, P == 1 ? 64 : L::E>{});
+  else if (small <= slots)
+    rc = launch(std::integral_constant<int, L::ESMALL>{});
+  else
     rc = launch(std::integral_constant<int, L::E>{});
-  }
   if (rc) return rc;
   k_gather_vertices<<<static_cast<unsigned>(ceil_div(sched->nrows, 256)), 256, 0, st>>>(
       dev_at<int32_t>(sched, sched->off_inc_ptr), dev_at<int32_t>(sched, sched->off_inc_list), sched->nrows, ework,
