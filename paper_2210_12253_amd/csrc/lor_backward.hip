@@ -105,8 +105,11 @@ struct BwLanes {
   static constexpr int E = P == 1 ? (F64 ? 32 : 16) : P == 2 ? 8 : P == 3 ? 2 : 1;
   // Half of that on a mesh whose groups are all resident at once even so: what a
   // group gathers in a row is then half as long (p = 1, 8^3 35 -> 29 us; p = 2, 4^3 36
-  // -> 31, but 20^3 90 -> 95).
+  // -> 31, but 20^3 90 -> 95).  p = 3 in FP32 (two waves for 27 subelements): only up to
+  // half of the chip's waves (9^3, batch 1: 21.5 us in pairs, 19.7 one by one, but 10^3
+  // 20.9 and 24.3, 11^3 21.5 and 27.9).
   static constexpr int ESMALL = P == 1 ? 16 : P == 2 ? 4 : 1;
+  static constexpr int SMALL_PART = P == 3 && !F64 ? 2 : 1;  // of the waves, one in so many
 };
 
 // p = 1: groups of 64 elements (one per lane) where smaller ones are the slower, with
@@ -481,7 +484,7 @@ static int launch_bw(const lor_sched* sched, int batch, const int32_t* elem_dofs
     return LOR_OK;
   };
   const int64_t slots = static_cast<int64_t>(4 * L::WPS) * num_cus_bw();  // waves
-  const int64_t small = ceil_div(nel, L::ESMALL) * (BwCfg<P, L::ESMALL>::LANES / 64 * L::H);
+  const int64_t small = ceil_div(nel, L::ESMALL) * (BwCfg<P, L::ESMALL>::LANES / 64 * L::H) * L::SMALL_PART;
   int rc;
   if (P == 1 && bw_one_per_lane(L::F64, nel, 64 * slots, batch))
     rc = launch(std::integral_constant<int, P == 1 ? 64 : L::E>{});

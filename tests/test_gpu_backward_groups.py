@@ -1,7 +1,8 @@
 """The backward kernel at p = 1 in groups of 64 elements (meshes just above half of what
 they take in one round of the chip, and in FP32 large ones with a small batch)
 against the oracle's autograd, and with the same coefficient gradients as in smaller
-groups, which the same mesh takes with a larger batch."""
+groups, which the same mesh takes with a larger batch; p = 3 on both sides of the line
+between groups of one and of two elements."""
 import pytest
 import torch
 
@@ -43,3 +44,15 @@ def test_groups_of_64(n, more):
         assert err(gx, gx_ref) <= tolx
         all_gk, _ = _gpu_grads(pat, m, kap, 0.7, cot, dt)
         assert torch.equal(all_gk[:1], gk)
+
+
+@pytest.mark.parametrize("n", [(32, 6, 4), (769, 1, 1), (11, 11, 11)])     # 768 (at most), 769 and 1,331 elements
+def test_groups_at_p3(n):
+    m = meshgen.box_mesh(*n, 3, 0.1)
+    kap = meshgen.kappa_field(m["nel"], 3, 1.0, seed=3, batch=2)
+    rp, ci, _ = orc.h1_matrix(m["coords"], m["elem_dofs"], 3, kap[0].detach(), 0.7)
+    cot = meshgen.cotangent(2, rp[-1].item(), seed=1)
+    gk_ref, gx_ref = oracle_loss_grads(m, 3, kap, 0.7, cot, rp, ci)
+    pat = lor.lor_pattern(lor.LOR_H1, 3, torch.from_numpy(m["elem_dofs"]).to(DEV), m["ndofs"])
+    gk, gx = _gpu_grads(pat, m, kap, 0.7, cot, torch.float32)
+    assert _rel(gk, gk_ref) <= 1e-5 and _rel(gx, gx_ref) <= 1e-5
