@@ -81,3 +81,26 @@ def test_h1_several_groups_per_workgroup(p, n, layers):
     for dt, tol in ((torch.float64, 1e-12), (torch.float32, 1e-6)):
         v = lor.lor_assemble_h1(pat, ed, x, kap.to(dt), 0.7, dtype=dt, kernel="colored")
         assert float(((v.double() - ref).abs() / largest[rows]).max()) <= tol
+
+
+@pytest.mark.parametrize("space,p,n,layers", [("nd", 4, 9, 9), ("nd", 5, 8, 9), ("rt", 5, 14, 10), ("rt", 6, 10, 8)])
+def test_vector_several_groups_per_workgroup(space, p, n, layers):
+    """The same for H(curl) and H(div) (256 to 1,024 resident workgroups): random rows
+    against the oracle, and symmetry."""
+    m = meshgen.tri_split_mesh(n, layers, p, 0.1)
+    kap = meshgen.kappa_field(m["nel"], p, 1.0, seed=1)
+    dm, nrows = (meshgen.edge_map_from_vertices if space == "nd" else meshgen.face_map_from_vertices)(m["elem_dofs"], p)
+    dm, _ = meshgen.flip_edge_signs(dm, nrows, seed=7)
+    ed, x, dmap = (torch.from_numpy(a).to(DEV) for a in (m["elem_dofs"], m["coords"], dm))
+    pat = lor.lor_pattern(lor.LOR_ND if space == "nd" else lor.LOR_RT, p, dmap, nrows)
+    ptr = list(pat.sched.color_ptr)[:pat.ncolors + 1]
+    assert max(b - a for a, b in zip(ptr, ptr[1:])) > {"nd": 256, "rt": 1024 if p == 5 else 512}[space]
+    pick = torch.randperm(nrows, generator=torch.Generator().manual_seed(p))[:300].sort().values
+    rows, rp, ci, v = (orc.nd_rows if space == "nd" else orc.rt_rows)(m["coords"], m["elem_dofs"], dm, p, kap, 0.7, pick)
+    asm = lor.lor_assemble_nd if space == "nd" else lor.lor_assemble_rt
+    full_rp = pat.row_ptr.cpu().long()
+    at = torch.cat([torch.arange(int(full_rp[r]), int(full_rp[r + 1])) for r in rows.tolist()])
+    for dt, tol in ((torch.float64, 1e-12), (torch.float32, 1e-6)):
+        got = asm(pat, ed, dmap, x, kap.to(dt), 0.7, m["ndofs"], dtype=dt, kernel="colored")
+        assert row_rel_err(rp, pat.col_idx.cpu()[at], got.cpu()[at], ci, v) <= tol
+        check_whole_matrix(pat, got)
