@@ -80,9 +80,14 @@ __host__ __device__ constexpr int pair_slot(int u, int v) {
   return n + v - u;
 }
 
-// Lanes per subelement (H) and waves per SIMD to reserve registers for (WPS).  The
-// kernel waits more than it computes (FP64, p = 4, batch 8: VALU issue in 36% of
-// a wave's cycles), so waves are what it wants, but a lane keeps 108 accumulators
+// What bounds the kernel at p = 4, 16^3, batch 8: HBM.  FP64 fetches 701 MB and writes
+// 29 in 162 us, 4.5 TB/s or 88% of a copy's rate (FP32 404 and 29 MB in 95 us or more);
+// about 200 MB of that are cotangent rows on element faces fetched again, for
+// neighbouring elements run on different XCDs, which share no L2.
+//
+// Lanes per subelement (H) and waves per SIMD to reserve registers for (WPS).  On
+// its way there it waits more than it computes (VALU issue in 36% of a wave's
+// cycles), so waves are what it wants, but a lane keeps 108 accumulators
 // (K, and the adjoints of K and M, per corner pair) and the next batch entry's
 // gathered cotangents.  FP32: two lanes share a subelement, each with 18 of the 36
 // pairs until the batch is through, and a register budget of two or three waves.

@@ -56,7 +56,6 @@ struct H1Cfg {
   static constexpr int MAXCHUNK = 256;                                 // elements per workgroup
   static_assert(RV <= 2, "two rows per lane");
   static_assert(E * NSUB <= THREADS, "one subelement per lane");
-  static_assert(NJ <= 64, "phase-3 mask");
 };
 
 // Resident workgroups per CU: as many as the LDS of one workgroup allows, up
@@ -510,7 +509,9 @@ extern "C" int lor_assemble_h1(int p, int64_t nel, int64_t ndofs, int batch, con
   // more where the elements are small.  Triangle-split meshes of 12 colours, rows
   // and colours, us: p = 1 22,500 cells per colour 136 and 253; p = 2 33,700 207
   // and 210; p = 3 19,600 126 and 121; p = 4 22,500 134 and 146, 28,500 165 and 155;
-  // p = 5 27,600 158 and 160; p = 6 27,200 152 and 158, 35,000 190 and 165.
+  // p = 5 27,600 158 and 160; p = 6 27,200 152 and 158, 35,000 190 and 165.  (p = 1
+  // has the line of p = 2, p = 4 and 5 that of p = 6: they cross at or above it, p = 1
+  // well above.)
   const int64_t per_color = p <= 2 ? 32000 : p == 3 ? 19000 : 26000;
   const bool rows = !owner && !(flags & LOR_COLORED) &&
                     rows_pay(sched, nel * p * p * p * static_cast<int64_t>(batch), per_color, 4);

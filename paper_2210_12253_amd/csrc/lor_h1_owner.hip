@@ -215,12 +215,12 @@ __global__ __launch_bounds__((OwnCfg<T, R, S>::THREADS), (OwnCfg<T, R, S>::WPE))
   const bool cell_in = cX < NXc && cY < NYc;
   const bool row_in = cX <= NXc && cY <= NYc;           // row (cX, cY) exists in every plane
   const bool row_own = row_in && (lx > 0 || ti == 0) && (ly > 0 || tj == 0);
-  // An inner tile (most of them): all 64 of its cells exist and, on an inner
-  // plane (0 < Z < NZc), every row it owns (x, y in [1, 7]) has all 27
+  // An inner tile (most of them): all S x S of its cells exist and, on an inner
+  // plane (0 < Z < NZc), every row it owns (x, y in [1, S - 1]) has all 27
   // neighbours.  Its steps on inner planes take a path without per-lane
   // conditions: the row sums read all four cells (lanes x = 0 or y = 0 read
   // clamped cells and own no row), each owned row is one 27-entry copy, and
-  // the seven owned lines of the plane are 7 rows x 27 entries each.
+  // the S - 1 owned lines of the plane are S - 1 rows x 27 entries each.
   const bool tile_inner = ti > 0 && tj > 0 && x0 + S <= NXc && y0 + S <= NYc;
   // lattice points of a plane: slot j -> point tid + THREADS j of the (S + 1) x (S + 1) grid
   auto pt_xy = [&](int j, int& X, int& Y) {

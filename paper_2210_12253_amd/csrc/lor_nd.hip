@@ -391,7 +391,8 @@ extern "C" int lor_assemble_nd(int p, int64_t nel, int64_t ndofs_h1, int64_t ned
   // Elsewhere (p <= 5): row by row on small meshes, in colours on large ones.
   // Triangle-split meshes of 9 colours, rows and colours: 5,800 cells per colour
   // 102 and 137 us (p = 3), 112 and 161 (p = 1); 8,800 149 and 141 us (p = 3);
-  // 8,000 137 and 251 (p = 5).  The line is where p = 3 crosses.
+  // 8,000 137 and 251 (p = 5); 15,400 284 and 251 (p = 1).  One line for all degrees,
+  // where the first of them, p = 3, crosses; the others cross above it.
   const bool rows = !owner && !(flags & LOR_COLORED) && p <= 5 &&
                     rows_pay(sched, nel * p * p * p * static_cast<int64_t>(batch), 8500, 4);
   if (rows)

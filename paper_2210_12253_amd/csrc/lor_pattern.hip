@@ -536,8 +536,9 @@ __global__ void k_sort_inc(const int32_t* __restrict__ inc_ptr, int32_t* __restr
 }
 
 // Columns of row g: the union of the local stencils of its incidences, by
-// inserting them into a hash table in LDS.  kRowColLanes lanes share a row; SLOTS
-// (a power of two) bounds the table, CAP the columns.  The short form (every row
+// inserting them into a hash table in LDS (slots by the golden-ratio multiplier).
+// kRowColLanes lanes share a row; SLOTS (a power of two) bounds the table, CAP the
+// columns.  The short form (every row
 // of the structured meshes and of the irregular test meshes fits) keeps many
 // waves per SIMD; a row that does not fit goes to the list `ovf` and is done again
 // by the full form.  `rows` (optional) lists the rows to do, else rows
@@ -880,7 +881,8 @@ __global__ void k_color_ptr(const int64_t* __restrict__ off, int nc, int64_t nbl
 
 // Table deduplication: elements whose rank tables are byte-identical share one
 // class.  A 64-bit hash of every element's table (one wave per element, a sum of
-// mixed words, so that lanes can take words in any order); a table of hashes that
+// mixed words, so that lanes can take words in any order; the multipliers of the
+// golden ratio and of splitmix64's finaliser); a table of hashes that
 // remembers the lowest element of each; classes numbered by first appearance.
 // Equality with the class representative is then verified word by word, so a
 // hash collision can only cost the deduplication, never correctness.

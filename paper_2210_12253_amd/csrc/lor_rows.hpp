@@ -1,13 +1,12 @@
-// Matrix values one row at a time, on any mesh: the part that H1 (3D and 2D),
-// H(curl) and H(div) share.
+// Matrix values one row at a time, on any mesh: the part that H1, H(curl) and H(div)
+// share (in 3D; the 2D call has no such kernel).
 //
 // The coloured kernels integrate every cell once, but need one launch per
 // colour, and on a small mesh each launch is the latency of one group (about
 // 11 us): 12 colours take 130 us whatever the mesh.  Here one launch does it:
 // S::LANES lanes sum one row, each integrating its share of the cells around
 // the row's vertex, edge or face, so every cell is integrated once per dof of
-// its own (8 vertices, 12 edges, 6 faces; 4 vertices in 2D), and every row is
-// stored once, whole.
+// its own (8 vertices, 12 edges, 6 faces), and every row is stored once, whole.
 //
 //   * The cells around a dof follow from its incidences (element, local dof),
 //     sorted in the schedule: within an element, in increasing number u of the

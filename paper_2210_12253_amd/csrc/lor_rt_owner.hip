@@ -21,8 +21,9 @@
 //   * every row type's finished rows of a line (X consecutive) are
 //     consecutive rows of the matrix: staged in LDS and stored as one span.
 //
-// What bounds it: one wave's step takes about 4 us, mostly the integration and the
-// latency between its phases, with two waves per SIMD (three spill: 67 us against
+// What bounds it: one wave's step takes about 7 us (p = 3, 24^3: six steps of one
+// round of waves, 48 us with the launch), mostly the integration and the latency between its
+// phases, with two waves per SIMD (three spill: 67 us against
 // 50).  Barriers that wait for LDS only, lines addressed by one lane each instead
 // of by scalar arithmetic in every step (125 spilled scalars), in FP64 columns by
 // one fused multiply-add per value and axis: p = 3, 24^3 56.7 -> 51.7 us, FP32 51.5
